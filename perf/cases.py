@@ -140,7 +140,8 @@ def _shards(t, mesh, spec, perm):
     out = []
     for box in _boxes(t.shape, mesh, spec):
         s = t[tuple(slice(lo, hi) for lo, hi in box)]
-        out.append(s.permute(perm).contiguous() if perm else s.contiguous())
+        # a buffer of its own, also where the slice is already dense
+        out.append((s.permute(perm) if perm else s).clone(memory_format=torch.contiguous_format))
     return out
 
 
