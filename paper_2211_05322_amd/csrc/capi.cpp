@@ -350,59 +350,67 @@ reshard_status_t reshard_debug_execute_host(const reshard_plan_t *plan, void *co
             const uint32_t levels = rs::kind_levels(d.kind);
             const size_t t0 = p->n_direct + p->n_gather + p->n_gather_u;
             if (di >= t0 && di < t0 + p->n_transpose) {
-                // tile-transpose chunk: the kernel's tile arithmetic and
-                // swizzled LDS tile, every access bounds-checked
-                const uint32_t es = uint32_t(p->es), te = rs::tile_elems(es), vpe = 16u / es;
-                const uint32_t tr = rs::tile_rows(es, d.kind), slots = tr * es / 16u;  // per column
-                const bool ald = (d.kind & rs::kTAlignLoad) != 0, ast = (d.kind & rs::kTAlignStore) != 0;
+                // tile-transpose chunk: the kernel's tile arithmetic and LDS
+                // image, every access bounds-checked
+                const uint32_t es = uint32_t(p->es), vpe = 16u / es, rg = es < 4 ? 4u / es : 1u;
+                const uint32_t vl2 = rs::tile_row_vecs_log2(d);
+                const uint32_t step_a = rs::tile_step_a(d), step_b = rs::tile_step_b(d);
+                const uint32_t slots = (step_b * es + 15u) / 16u, sp = rs::tile_slots_padded(slots);
                 if ((1u << (d.kind & 0xFu)) != es) return fail(RESHARD_EINVAL, "internal: transpose element size");
+                if (step_a == 0 || step_b == 0 || step_a * es > (16u << vl2))
+                    return fail(RESHARD_EINVAL, "internal: transpose tile extents");
                 const uint64_t sbytes = uint64_t(p->src_local_numel[d.src_buf] * p->es);
-                lds.assign(tr * rs::kTileBytes, 0);
+                const uint32_t each = rs::tile_lds_bytes(step_a, step_b, es);
+                if (uint64_t(each) * (d.v1 - d.v0) > p->transpose_lds)
+                    return fail(RESHARD_EINVAL, "internal: transpose tiles larger than their LDS");
+                lds.assign(each, 0);
+                auto out = [&](uint64_t off, const uint8_t *y, uint32_t n) {
+                    for (uint32_t r = 0; r < d.nfan; ++r) {
+                        const int32_t dev = p->fan[d.fan_off + r];
+                        if (off + n > uint64_t(p->dst_local_numel[dev] * p->es)) return false;
+                        std::memcpy(static_cast<char *>(dst_ptrs[dev]) + off, y, n);
+                    }
+                    return true;
+                };
                 for (uint32_t t = d.v0; t < d.v1; ++t) {
                     const rs::TileAt at = rs::tile_offsets(d, t, es);
-                    const uint32_t na = std::min(te, d.run - at.ta * te), nb = std::min(tr, d.batch - at.tb * tr);
-                    for (uint32_t i = 0; i < tr * 8u; ++i) {  // load phase
-                        const uint32_t r = i >> 3, c = i & 7u;
-                        if (r >= nb) continue;
-                        const uint32_t a0 = c * vpe;
-                        const uint32_t nv = a0 < na ? std::min(vpe, na - a0) : 0u;
+                    const uint32_t ra = d.run - at.ta * step_a, na = std::min(ra, step_a);
+                    const uint32_t nb = std::min(step_b, d.batch - at.tb * step_b);
+                    const uint32_t nvec = (na + vpe - 1) / vpe;
+                    for (uint32_t i = 0; i < (nb + rg - 1) / rg * rg * nvec; ++i) {  // load phase
+                        const uint32_t b = i / nvec, r = std::min(b, nb - 1), c = i % nvec;
+                        const uint32_t n = std::min<uint32_t>(16u, (ra - c * vpe) * es);
                         uint8_t x[16] = {0};
                         const uint64_t q = d.src_base + uint32_t(at.src + r * d.ss[0] + c * 16u);
-                        if (nv == vpe && ald) {
-                            if (q % 16 != 0) return fail(RESHARD_EINVAL, "internal: transpose vector load misaligned");
-                            if (q + 16 > sbytes) return fail(RESHARD_EINVAL, "internal: transpose load outside its source shard");
-                            std::memcpy(x, static_cast<const char *>(src_ptrs[d.src_buf]) + q, 16);
-                        } else {
-                            for (uint32_t e = 0; e < nv; ++e) {
-                                if (q + (e + 1) * es > sbytes) return fail(RESHARD_EINVAL, "internal: transpose load outside its source shard");
-                                std::memcpy(x + e * es, static_cast<const char *>(src_ptrs[d.src_buf]) + q + e * es, es);
-                            }
-                        }
-                        const uint32_t o = rs::tile_lds(r, c, 0, es);
-                        if (o + 16 > lds.size()) return fail(RESHARD_EINVAL, "internal: transpose LDS write out of range");
-                        std::memcpy(lds.data() + o, x, 16);
-                    }
-                    for (uint32_t i = 0; i < te * slots; ++i) {  // store phase
-                        const uint32_t a = i / slots, j = i % slots;
-                        if (a >= na) continue;
-                        const uint32_t b0 = j * vpe;
-                        const uint32_t nv = b0 < nb ? std::min(vpe, nb - b0) : 0u;
-                        if (nv == 0) continue;
-                        uint8_t y[16] = {0};
+                        if (q + n > sbytes) return fail(RESHARD_EINVAL, "internal: transpose load outside its source shard");
+                        std::memcpy(x, static_cast<const char *>(src_ptrs[d.src_buf]) + q, n);
                         for (uint32_t e = 0; e < vpe; ++e) {
-                            const uint32_t o = rs::tile_lds(b0 + e, (a * es) >> 4, (a * es) & 15u, es);
-                            if (o + es > lds.size()) return fail(RESHARD_EINVAL, "internal: transpose LDS read out of range");
-                            std::memcpy(y + e * es, lds.data() + o, es);
+                            const uint32_t a = c * vpe + e;
+                            const uint32_t o = a * (16u * sp) + ((((b * es) >> 4) ^ rs::tile_swizzle(a, sp, es)) << 4) +
+                                               ((b * es) & 15u);
+                            if (o + es > lds.size()) return fail(RESHARD_EINVAL, "internal: transpose LDS write out of range");
+                            std::memcpy(lds.data() + o, x + e * es, es);
                         }
-                        for (uint32_t r = 0; r < d.nfan; ++r) {
-                            const int32_t dev = p->fan[d.fan_off + r];
-                            const uint64_t dbytes = uint64_t(p->dst_local_numel[dev] * p->es);
-                            const uint64_t q = d.dst_base + uint32_t(at.dst + a * d.ds[0] + j * 16u);
-                            if (nv == vpe && ast && q % 16 != 0)
-                                return fail(RESHARD_EINVAL, "internal: transpose vector store misaligned");
-                            if (q + nv * es > dbytes) return fail(RESHARD_EINVAL, "internal: transpose store outside its destination shard");
-                            std::memcpy(static_cast<char *>(dst_ptrs[dev]) + q, y, nv * es);
+                    }
+                    // store phase
+                    for (uint32_t i = 0; i < na * slots; ++i) {
+                        const uint32_t a = rs::fastdiv(i, d.pad[1], rs::tile_slot_shift(d));
+                        uint32_t b0 = (i - a * slots) * vpe;
+                        if (b0 >= nb) continue;
+                        uint32_t nv = std::min(vpe, nb - b0);
+                        if (nv < vpe && nb >= vpe) {
+                            b0 = nb - vpe;
+                            nv = vpe;
                         }
+                        uint8_t y[16] = {0};
+                        for (uint32_t k = 0; k < nv * es; ++k) {
+                            const uint32_t o = b0 * es + k;
+                            const uint32_t at_lds = a * (16u * sp) + (((o >> 4) ^ rs::tile_swizzle(a, sp, es)) << 4) + (o & 15u);
+                            if (at_lds >= lds.size()) return fail(RESHARD_EINVAL, "internal: transpose LDS read out of range");
+                            y[k] = lds[at_lds];
+                        }
+                        if (!out(d.dst_base + uint32_t(at.dst + a * d.ds[0] + b0 * es), y, nv * es))
+                            return fail(RESHARD_EINVAL, "internal: transpose store outside its destination shard");
                     }
                 }
                 continue;

@@ -155,33 +155,30 @@ constexpr uint32_t kMaxSegs = 256;  // segment entries one gather chunk may stag
 // Tile-transpose path (own section and kernel), for tasks whose source and
 // destination layouts are contiguous along different tensor dimensions (a
 // permuted local layout): A is the dimension contiguous in the sender's
-// buffer, B the one contiguous in the receivers'.  A tile is kTileBytes /
-// es elements along each of A and B: its rows (one per B index) are
-// kTileBytes contiguous source bytes, its columns (one per A index)
-// kTileBytes contiguous destination bytes.  A chunk is a range of tiles of a
-// piece (tile t: tb = t mod ntb fastest, then ta, then the outer levels o1,
-// o2).  Fields: kind = log2 es | kTAlignLoad | kTAlignStore | (log2 of the
-// width factor along B) << 6; ss[0] = sender
-// stride of B, ds[0] = receiver stride of A; ss[1], ds[1] and ss[2], ds[2]
-// the outer levels o1 (inner) and o2; vpr = ntb, n1 = nta, n2 = extent of o1
-// (with their fast divisions); run = extent of A, batch = extent of B
+// buffer, B the one contiguous in the receivers'.  A tile is step_a elements
+// along A by step_b along B: its rows (one per B index) are contiguous
+// source bytes, its columns (one per A index) contiguous destination bytes.
+// A chunk is a range of tiles of a piece (tile t: tb = t mod ntb fastest,
+// then ta, then the outer levels o1, o2).  Fields: kind = log2 es; ss[0] =
+// sender stride of B, ds[0] = receiver stride of A; ss[1], ds[1] and ss[2],
+// ds[2] the outer levels o1 (inner) and o2; vpr = ntb, n1 = nta, n2 = extent
+// of o1 (with their fast divisions); run = extent of A, batch = extent of B
 // (elements); v0, v1 the tiles; src_base/dst_base, src_rel0/dst_rel0 as
-// usual, for tile v0's origin.  The aligned flags say that every tile row
-// (column) starts on a 16-byte boundary, so whole 16-byte vectors of it are
-// loaded (stored) at once; otherwise elements move one by one.
-constexpr uint32_t kTileBytes = 128;
-constexpr uint32_t kTAlignLoad = 0x10u;
-constexpr uint32_t kTAlignStore = 0x20u;
+// usual, for the piece's origin; pad[0] = log2 of the 16-byte vectors an LDS
+// tile row holds | shift << 8, pad[1] = multiplier of the fast division by
+// the 16-byte slots of a whole tile column; pad[2] = step_a | step_b << 16.
+// Rows and columns may start at any element: vectors are loaded and stored
+// at any byte address, and a vector cut by the end of its row or column is
+// handled on its own (kernel).
+constexpr uint32_t kTileBytes = 128;  // nominal tile row: one cache line
 constexpr uint32_t tile_elems(uint32_t es) { return kTileBytes / es; }
-// A tile spans 1, 2 or 4 x kTileBytes along B (kind bits 6-7 hold log2 of
-// that factor): wide enough to write whole destination rows of up to 512
-// bytes, so each tile fills every cache line of the rows it writes.  Its
-// LDS image is (B extent) rows of kTileBytes.
-constexpr uint32_t tile_wide_log2(uint32_t kind) { return (kind >> 6) & 3u; }
-constexpr uint32_t tile_rows(uint32_t es, uint32_t kind) { return tile_elems(es) << tile_wide_log2(kind); }
+constexpr uint32_t tile_step_a(const Desc &d) { return d.pad[2] & 0xFFFFu; }
+constexpr uint32_t tile_step_b(const Desc &d) { return d.pad[2] >> 16; }
+constexpr uint32_t tile_row_vecs_log2(const Desc &d) { return d.pad[0] & 0xFFu; }
+constexpr uint32_t tile_slot_shift(const Desc &d) { return d.pad[0] >> 8; }
 
 // Relative offsets (sender, receiver) of tile t's origin from the chunk's
-// first tile (mod 2^32), and the tile's (ta, tb) indices.
+// base (mod 2^32), and the tile's (ta, tb) indices.
 struct TileAt {
     uint32_t src, dst, ta, tb;
 };
@@ -193,20 +190,26 @@ constexpr TileAt tile_offsets(const Desc &d, uint32_t t, uint32_t es) {
     const uint32_t ta = r - o * d.n1;
     const uint32_t o2 = fastdiv(o, d.mul_n2, d.sh_n2);
     const uint32_t o1 = o - o2 * d.n2;
-    const uint32_t te = tile_elems(es), tr = tile_rows(es, d.kind);
-    const uint32_t s = tb * tr * d.ss[0] + ta * kTileBytes + o1 * d.ss[1] + o2 * d.ss[2];
-    const uint32_t u = ta * te * d.ds[0] + tb * (tr * es) + o1 * d.ds[1] + o2 * d.ds[2];
+    const uint32_t pa = ta * tile_step_a(d), pb = tb * tile_step_b(d);
+    const uint32_t s = pb * d.ss[0] + pa * es + o1 * d.ss[1] + o2 * d.ss[2];
+    const uint32_t u = pa * d.ds[0] + pb * es + o1 * d.ds[1] + o2 * d.ds[2];
     return TileAt{s - d.src_rel0, u - d.dst_rel0, ta, tb};
 }
 
-// LDS byte offset of byte `o` of 16-byte column slot c in tile row r: rows
-// are kTileBytes apart, and the slot is XOR-swizzled by the row's group of
-// 16 / es rows, so the column reads of the store phase (16 / es rows of one
-// slot per output vector) of a 128-byte-wide tile hit distinct banks.  In
-// wider tiles 32 lanes read one column through 8 slots and conflict; a
-// conflict-free lane order measured no faster (the kernel is not LDS-bound).
-constexpr uint32_t tile_lds(uint32_t r, uint32_t c, uint32_t o, uint32_t es) {
-    return r * kTileBytes + ((c ^ ((r / (16u / es)) & 7u)) << 4) + o;
+// LDS image of a tile, already transposed: tile column a (16 / es rows of the
+// tile make one 16-byte slot of it) at a * tile_col_bytes, its slot j at slot
+// j ^ tile_swizzle(a): the load phase writes dwords of 16 / es neighbouring
+// columns (and 8 neighbouring vectors) at once, which the exchange spreads
+// over the banks.   Columns are counted in whole
+// vectors of rows.
+constexpr uint32_t tile_slots_padded(uint32_t slots) {
+    return slots > 4u ? (slots + 7u) & ~7u : slots > 2u ? 4u : slots;
+}
+constexpr uint32_t tile_swizzle(uint32_t a, uint32_t slots_padded, uint32_t es) {
+    return (a / (16u / es)) & (slots_padded >= 8u ? 7u : slots_padded - 1u);
+}
+constexpr uint32_t tile_lds_bytes(uint32_t step_a, uint32_t step_b, uint32_t es) {
+    return (step_a * es + 15u) / 16u * (16u / es) * 16u * tile_slots_padded((step_b * es + 15u) / 16u);
 }
 
 // Outer-level indices of a row (level 1 = innermost outer level).

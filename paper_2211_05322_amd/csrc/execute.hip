@@ -14,6 +14,8 @@
 //   reshard_gather_u_kernel unaligned row gather: 16-byte slots of the
 //                           receivers' buffers built from at most two
 //                           misaligned pieces (segments of any width >= 16 B);
+//   reshard_transpose_kernel tiles between layouts contiguous along
+//                           different dimensions, transposed through LDS;
 //   reshard_realign_kernel  rows in different 16-byte phases, one task at a
 //                           time (shifted loads, or staging through LDS).
 // Loads of a batch are issued before its stores so each lane keeps several
@@ -25,7 +27,9 @@
 // space so they land in scalar registers.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
+#include <type_traits>
 
 #include "../../include/reshard.h"
 #include "planner.hpp"
@@ -54,7 +58,7 @@ struct KArgs {
     uint32_t ndesc;
     uint32_t nsrc;     // ptr[0, nsrc) are source buffers, ptr[nsrc, ...) destination buffers
     uint32_t per_xcd;  // > 0: XCD x runs chunks [x*per_xcd, (x+1)*per_xcd)
-    uint32_t pad;
+    uint32_t group;    // transpose: consecutive chunks per XCD
     void *ptr[NPTR];
 };
 
@@ -980,183 +984,247 @@ __global__ __launch_bounds__(256) void reshard_gather_u_kernel(KArgs<NPTR> args)
     }
 }
 
-// Tile transpose (see desc.h): per tile, a load phase (rows of the tile,
-// contiguous in the sender's buffer, into LDS: 16-byte vectors where the
-// rows are aligned, else element by element) and a store phase (columns of
-// the tile, contiguous in the receivers' buffers: each lane assembles one
-// 16-byte vector from 16 / ES rows of one column and stores it to every
-// receiver).  Lanes 8k .. 8k + 7 cover one row (one column) of 128 bytes,
-// so a wave moves 8 whole cache lines per instruction on both sides.
-template <int ES>
-__device__ __forceinline__ void tile_put(unsigned char *lds, uint32_t off, u32x4 v) {
-    *reinterpret_cast<u32x4 *>(lds + off) = v;
-}
-
-template <int ES>
-__device__ __forceinline__ u32x4 tile_column(const unsigned char *lds, uint32_t b0, uint32_t a) {
-    const uint32_t c = (a * ES) >> 4, o = (a * ES) & 15u;
-    if constexpr (ES == 8) {
-        u32x4 y;
-        const u32x2 lo = *reinterpret_cast<const u32x2 *>(lds + tile_lds(b0, c, o, ES));
-        const u32x2 hi = *reinterpret_cast<const u32x2 *>(lds + tile_lds(b0 + 1, c, o, ES));
-        y.x = lo.x; y.y = lo.y; y.z = hi.x; y.w = hi.y;
-        return y;
-    } else if constexpr (ES == 4) {
-        u32x4 y;
-        y.x = *reinterpret_cast<const uint32_t *>(lds + tile_lds(b0, c, o, ES));
-        y.y = *reinterpret_cast<const uint32_t *>(lds + tile_lds(b0 + 1, c, o, ES));
-        y.z = *reinterpret_cast<const uint32_t *>(lds + tile_lds(b0 + 2, c, o, ES));
-        y.w = *reinterpret_cast<const uint32_t *>(lds + tile_lds(b0 + 3, c, o, ES));
-        return y;
+// The low n bytes (0 < n < 16) of y to q (any byte address): two stores of the
+// largest power of two up to n, the second ending at byte n (it rewrites
+// equal bytes where they overlap).
+__device__ __forceinline__ void store_low(RS_GLOBAL unsigned char *q, u32x4 y, uint32_t n) {
+    typedef uint64_t u64_u __attribute__((aligned(1)));
+    typedef uint32_t u32_u __attribute__((aligned(1)));
+    typedef uint16_t u16_u __attribute__((aligned(1)));
+    const uint64_t lo = (uint64_t(y.y) << 32) | y.x, hi = (uint64_t(y.w) << 32) | y.z;
+    const uint32_t p = n >= 8u ? 8u : n >= 4u ? 4u : n >= 2u ? 2u : 1u;
+    const uint32_t s = 8u * (n - p);  // the second piece: bits [s, s + 8 p) of hi:lo, s < 64
+    const uint64_t t = s == 0 ? lo : (lo >> s) | (hi << (64u - s));
+    if (p == 8u) {
+        *(RS_GLOBAL u64_u *)q = lo;
+        *(RS_GLOBAL u64_u *)(q + (n - p)) = t;
+    } else if (p == 4u) {
+        *(RS_GLOBAL u32_u *)q = uint32_t(lo);
+        *(RS_GLOBAL u32_u *)(q + (n - p)) = uint32_t(t);
+    } else if (p == 2u) {
+        *(RS_GLOBAL u16_u *)q = uint16_t(lo);
+        *(RS_GLOBAL u16_u *)(q + (n - p)) = uint16_t(t);
     } else {
-        uint32_t w[4];
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) {
-            uint32_t acc = 0;
-#pragma unroll
-            for (uint32_t e = 0; e < 4 / ES; ++e) {
-                const uint32_t r = b0 + q * (4 / ES) + e;
-                uint32_t x;
-                if constexpr (ES == 2) x = *reinterpret_cast<const uint16_t *>(lds + tile_lds(r, c, o, ES));
-                else x = lds[tile_lds(r, c, o, ES)];
-                acc |= x << (8u * ES * e);
-            }
-            w[q] = acc;
-        }
-        u32x4 y;
-        y.x = w[0]; y.y = w[1]; y.z = w[2]; y.w = w[3];
-        return y;
+        *q = (unsigned char)lo;
     }
 }
 
-template <int ES> struct Elem;
-template <> struct Elem<1> { typedef unsigned char T; };
-template <> struct Elem<2> { typedef unsigned short T; };
-template <> struct Elem<4> { typedef unsigned int T; };
-template <> struct Elem<8> { typedef unsigned long long T; };
+// Tile transpose (see desc.h): a load phase (rows of the tile, contiguous in
+// the sender's buffer, transposed into LDS) and a store phase (16-byte slots
+// of the tile's columns, contiguous in the receivers' buffers).  A lane loads
+// one vector from each of R = 4 / ES (at least 1) neighbouring rows and
+// exchanges their elements in registers, so it writes LDS in dwords (8 bytes
+// for ES 8) that hold R neighbouring elements of a column, and reads whole
+// slots; consecutive lanes then store consecutive slots of a column.
+// Vectors move at any byte address, so rows and columns that start off
+// 16-byte boundaries cost the same instructions as aligned ones (measured
+// against one load and store per element, which such sides took before:
+// bf16 [8,2047,4098] to [batch, hidden, seq], one receiver, 107.6 -> 57 us,
+// 2.5 -> 4.7 TB/s; uint8 [58,152,25544] to 8 receivers 2350 -> 425 us).
+//
+// What is left is HBM's: columns that do not start on 64-byte boundaries
+// write the two ends of each column of each tile as parts of what memory
+// writes at once.  PLAIN kernels (the plan has such tiles) store them through
+// L2, and take kTGroup consecutive chunks on one XCD, so that a neighbouring
+// tile's part meets them there (fp16 [23,1008,8640] (4,8) R S^1 R -> R R
+// S^{01}: non-temporal stores, chunks in turn 335 us; plain stores 256; runs
+// of 8 chunks 235; both 198).  Other tiles keep non-temporal stores, which
+// beat plain ones there (int64 650 x 4480 transposed to 8 receivers 35
+// against 42 us).  Runs of 32 and 64 were level with 16 on large plans; with
+// few chunks they leave XCDs idle.
+constexpr uint32_t kTGroup = 16;
+// Least LDS per workgroup for plans of 4096 tiles or more: 6 workgroups per
+// CU (measured against uncapped, [8,2047,4098] above 59.7 -> 57.0 us, with 4
+// 56.9, with 2 72.0; fp16 [5,176,48,5376] at fan-out 2 263 -> 260, 281, 396).
+constexpr uint32_t kTLeastLds = 27000;
 
-// The first n (< 16 / ES) elements at q, one load each, packed into a
-// 16-byte value (the rest zero).  Unrolled with constant indices, so the
-// value stays in registers.
-template <int ES>
-__device__ __forceinline__ u32x4 load_elems(const RS_GLOBAL unsigned char *q, uint32_t n) {
-    typedef typename Elem<ES>::T E;
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+// tile_put: the vectors x of rows b .. b + R - 1 (b a multiple of R), tile
+// columns a0 .. a0 + 16 / ES - 1, to the LDS image.
+template <int ES, int R>
+__device__ __forceinline__ void tile_put(unsigned char *lds, const u32x4 (&x)[R], uint32_t a0, uint32_t b, uint32_t sp) {
+    unsigned char *q = lds + a0 * (16u * sp) + ((((b * ES) >> 4) ^ tile_swizzle(a0, sp, ES)) << 4) + ((b * ES) & 15u);
+    const uint32_t cb = 16u * sp;  // bytes per column
+    if constexpr (ES == 8) {
+        u32x2 lo, hi;
+        lo.x = x[0].x; lo.y = x[0].y; hi.x = x[0].z; hi.y = x[0].w;
+        *reinterpret_cast<u32x2 *>(q) = lo;
+        *reinterpret_cast<u32x2 *>(q + cb) = hi;
+    } else if constexpr (ES == 4) {
 #pragma unroll
-    for (uint32_t e = 0; e < 16u / ES; ++e) {
-        if (e < n) {
-            const E v = ((const RS_GLOBAL E *)q)[e];
-            if constexpr (ES == 8) {
-                w[2 * e] = uint32_t(v);
-                w[2 * e + 1] = uint32_t(uint64_t(v) >> 32);
-            } else {
-                w[(e * ES) / 4] |= uint32_t(v) << (8u * ((e * ES) % 4));
-            }
+        for (uint32_t i = 0; i < 4; ++i) *reinterpret_cast<uint32_t *>(q + i * cb) = x[0][i];
+    } else if constexpr (ES == 2 && R == 1) {
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            *reinterpret_cast<uint16_t *>(q + (2 * i) * cb) = uint16_t(x[0][i]);
+            *reinterpret_cast<uint16_t *>(q + (2 * i + 1) * cb) = uint16_t(x[0][i] >> 16);
+        }
+    } else if constexpr (ES == 2) {
+        // v_perm_b32: selector bytes 0-3 pick from the second operand, 4-7 from the first
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            *reinterpret_cast<uint32_t *>(q + (2 * i) * cb) = __builtin_amdgcn_perm(x[1][i], x[0][i], 0x05040100u);
+            *reinterpret_cast<uint32_t *>(q + (2 * i + 1) * cb) = __builtin_amdgcn_perm(x[1][i], x[0][i], 0x07060302u);
+        }
+    } else {
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {  // a 4 x 4 byte block
+            const uint32_t t0 = __builtin_amdgcn_perm(x[1][i], x[0][i], 0x05010400u);
+            const uint32_t t1 = __builtin_amdgcn_perm(x[1][i], x[0][i], 0x07030602u);
+            const uint32_t u0 = __builtin_amdgcn_perm(x[3][i], x[2][i], 0x05010400u);
+            const uint32_t u1 = __builtin_amdgcn_perm(x[3][i], x[2][i], 0x07030602u);
+            *reinterpret_cast<uint32_t *>(q + (4 * i) * cb) = __builtin_amdgcn_perm(u0, t0, 0x05040100u);
+            *reinterpret_cast<uint32_t *>(q + (4 * i + 1) * cb) = __builtin_amdgcn_perm(u0, t0, 0x07060302u);
+            *reinterpret_cast<uint32_t *>(q + (4 * i + 2) * cb) = __builtin_amdgcn_perm(u1, t1, 0x05040100u);
+            *reinterpret_cast<uint32_t *>(q + (4 * i + 3) * cb) = __builtin_amdgcn_perm(u1, t1, 0x07060302u);
         }
     }
-    u32x4 x;
-    x.x = w[0]; x.y = w[1]; x.z = w[2]; x.w = w[3];
-    return x;
 }
 
-// Store the first n (< 16 / ES) elements of y at q, one store each.
-template <int ES>
-__device__ __forceinline__ void store_elems(RS_GLOBAL unsigned char *q, u32x4 y, uint32_t n) {
-    typedef typename Elem<ES>::T E;
-    const uint32_t w[4] = {y.x, y.y, y.z, y.w};
-#pragma unroll
-    for (uint32_t e = 0; e < 16u / ES; ++e) {
-        if (e < n) {
-            E v;
-            if constexpr (ES == 8) v = E(w[2 * e]) | (E(w[2 * e + 1]) << 32);
-            else v = E(w[(e * ES) / 4] >> (8u * ((e * ES) % 4)));
-            ((RS_GLOBAL E *)q)[e] = v;
+// One 16-byte vector of a tile row; n: bytes of the source row from q on.
+__device__ __forceinline__ u32x4 tile_load(const RS_GLOBAL unsigned char *q, uint32_t n) {
+    if (n >= 16u) return *(const RS_GLOBAL u32x4_u *)q;
+    return load_short(q, n);
+}
+
+// Slot at rows b0 .. of tile column aa to the receivers.
+template <int ES, bool PLAIN, int NPTR>
+__device__ __forceinline__ void tile_store(const Desc &d, const RS_CONST KArgs<NPTR> *a, const RS_CONST int32_t *fan,
+                                           const unsigned char *lds, uint32_t sp, uint32_t dst, uint32_t nb,
+                                           uint32_t aa, uint32_t b0) {
+    constexpr uint32_t V = 16u / ES;
+    const uint32_t sw = tile_swizzle(aa, sp, ES);
+    const u32x4 *col = reinterpret_cast<const u32x4 *>(lds + aa * (16u * sp));
+    u32x4 y = col[((b0 * ES) >> 4) ^ sw];
+    uint32_t nv = nb - b0 < V ? nb - b0 : V;
+    if (nv < V && nb >= V) {  // the column's last vector, moved back: it rewrites equal bytes
+        const uint32_t o = (nb - V) * ES;
+        y = funnel32(col[(o >> 4) ^ sw], y, o & 15u);
+        b0 = nb - V;
+        nv = V;
+    }
+    const uint32_t off = dst + aa * d.ds[0] + b0 * ES;
+    if (nv == V) {
+        for (uint32_t r = 0; r < d.nfan; ++r) {
+            RS_GLOBAL u32x4_u *q = (RS_GLOBAL u32x4_u *)((RS_GLOBAL char *)a->ptr[a->nsrc + uint32_t(fan[r])] + d.dst_base + off);
+            if constexpr (PLAIN) *q = y;
+            else __builtin_nontemporal_store(y, q);
         }
+    } else {
+        for (uint32_t r = 0; r < d.nfan; ++r)
+            store_low((RS_GLOBAL unsigned char *)a->ptr[a->nsrc + uint32_t(fan[r])] + d.dst_base + off, y, nv * ES);
     }
 }
 
-// G: tile-row vectors per lane loaded before any is written to LDS.
-// Measured on an fp16 [8,2048,12288] transpose: 4 is 4 % faster than 1 at
-// fan-out 1, where reads are half of a tile's traffic; at fan-out 4 it
-// measured from 2 % slower to equal, so only one receiver uses it.
-template <int ES, uint32_t G, int NPTR>
+// R: tile rows a lane loads and exchanges together; G: groups of R vectors
+// per lane loaded before any is written to LDS.
+template <int ES, uint32_t R, uint32_t G, bool PLAIN, int NPTR>
 __device__ __forceinline__ void run_transpose(const Desc &d, const RS_CONST KArgs<NPTR> *a) {
-    constexpr uint32_t T = kTileBytes / ES, V = 16u / ES;
-    const uint32_t TR = tile_rows(ES, d.kind), SL = TR * ES / 16u;  // tile rows; 16-byte slots per column
+    constexpr uint32_t V = 16u / ES;
     unsigned char *lds = rs_lds;
     const RS_GLOBAL unsigned char *src = (const RS_GLOBAL unsigned char *)a->ptr[d.src_buf] + d.src_base;
     const RS_CONST int32_t *fan = (const RS_CONST int32_t *)(a->fan + d.fan_off);
-    const bool ald = (d.kind & kTAlignLoad) != 0, ast = (d.kind & kTAlignStore) != 0;
     const uint32_t nthr = blockDim.x, tid = threadIdx.x;
-    const uint32_t wl2 = tile_wide_log2(d.kind);
-    for (uint32_t t = d.v0; t < d.v1; ++t) {
-        const TileAt at = tile_offsets(d, t, ES);
-        const uint32_t na = d.run - at.ta * T < T ? d.run - at.ta * T : T;
-        const uint32_t nb = d.batch - at.tb * TR < TR ? d.batch - at.tb * TR : TR;
-        for (uint32_t i0 = tid; i0 < TR * 8u; i0 += G * nthr) {
-            u32x4 x[G];
+    const uint32_t vl2 = tile_row_vecs_log2(d), vmask = (1u << vl2) - 1u;
+    const uint32_t step_a = tile_step_a(d), step_b = tile_step_b(d);
+    const uint32_t slots = (step_b * ES + 15u) / 16u, sp = tile_slots_padded(slots);
+    if (d.v1 - d.v0 == 1u) {
+        const TileAt at = tile_offsets(d, d.v0, ES);
+        const uint32_t ra = d.run - at.ta * step_a;  // elements from here to the end of the source row
+        const uint32_t na = ra < step_a ? ra : step_a;
+        const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
+        const uint32_t nvec = (na + V - 1u) / V, total = (nb + R - 1u) / R << vl2;
+        if (nvec * V <= ra) {
+            // every vector of the tile's rows lies inside its source row:
+            // lanes past the tile repeat its last vectors, so the loads of a
+            // group carry no branches
+            for (uint32_t i0 = tid; i0 < total; i0 += G * nthr) {
+                u32x4 x[G][R];
 #pragma unroll
-            for (uint32_t k = 0; k < G; ++k) {
-                const uint32_t i = i0 + k * nthr, r = i >> 3, c = i & 7u;
-                if (i >= TR * 8u || r >= nb) continue;
-                const uint32_t a0 = c * V;
-                const uint32_t nv = a0 < na ? (na - a0 < V ? na - a0 : V) : 0u;
-                const RS_GLOBAL unsigned char *q = src + (at.src + r * d.ss[0] + c * 16u);
-                if (nv == V && ald) x[k] = load_vec((const RS_GLOBAL u32x4 *)q);
-                else x[k] = load_elems<ES>(q, nv);
-            }
+                for (uint32_t k = 0; k < G; ++k) {
+                    uint32_t i = i0 + k * nthr;
+                    i = i < total ? i : total - 1u;
+                    uint32_t c = i & vmask;
+                    c = c < nvec ? c : nvec - 1u;
 #pragma unroll
-            for (uint32_t k = 0; k < G; ++k) {
-                const uint32_t i = i0 + k * nthr, r = i >> 3, c = i & 7u;
-                if (i < TR * 8u && r < nb) tile_put<ES>(lds, tile_lds(r, c, 0, ES), x[k]);
-            }
-        }
-        __syncthreads();
-        for (uint32_t i = tid; i < T * SL; i += nthr) {
-            const uint32_t aa = i >> (3u + wl2), j = i & (SL - 1u);
-            if (aa >= na) continue;
-            const uint32_t b0 = j * V;
-            const uint32_t nv = b0 < nb ? (nb - b0 < V ? nb - b0 : V) : 0u;
-            if (nv == 0) continue;
-            const u32x4 y = tile_column<ES>(lds, b0, aa);
-            const uint32_t off = at.dst + aa * d.ds[0] + j * 16u;
-            if (nv == V && ast) {
-                for (uint32_t r = 0; r < d.nfan; ++r) {
-                    RS_GLOBAL char *dst = (RS_GLOBAL char *)a->ptr[a->nsrc + uint32_t(fan[r])] + d.dst_base;
-                    store_vec((RS_GLOBAL u32x4 *)(dst + off), y);
+                    for (uint32_t q = 0; q < R; ++q) {
+                        uint32_t r = (i >> vl2) * R + q;
+                        r = r < nb ? r : nb - 1u;
+                        x[k][q] = *(const RS_GLOBAL u32x4_u *)(src + (at.src + r * d.ss[0] + c * 16u));
+                    }
                 }
-            } else {
-                for (uint32_t r = 0; r < d.nfan; ++r)
-                    store_elems<ES>((RS_GLOBAL unsigned char *)a->ptr[a->nsrc + uint32_t(fan[r])] + d.dst_base + off,
-                                    y, nv);
+#pragma unroll
+                for (uint32_t k = 0; k < G; ++k) {
+                    const uint32_t i = i0 + k * nthr, c = i & vmask;
+                    if (i < total && c < nvec) tile_put<ES, R>(lds, x[k], c * V, (i >> vl2) * R, sp);
+                }
+            }
+        } else {
+            // the tile at the rows' end: the last vector of each is short
+            for (uint32_t i = tid; i < total; i += nthr) {
+                const uint32_t c = i & vmask;
+                if (c >= nvec) continue;
+                u32x4 x[R];
+#pragma unroll
+                for (uint32_t q = 0; q < R; ++q) {
+                    uint32_t r = (i >> vl2) * R + q;
+                    r = r < nb ? r : nb - 1u;
+                    x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
+                }
+                tile_put<ES, R>(lds, x, c * V, (i >> vl2) * R, sp);
             }
         }
         __syncthreads();
+        for (uint32_t i = tid; i < na * slots; i += nthr) {
+            const uint32_t aa = fastdiv(i, d.pad[1], tile_slot_shift(d)), b0 = (i - aa * slots) * V;
+            if (b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds, sp, at.dst, nb, aa, b0);
+        }
+    } else {
+        // small tiles, all of the chunk at once, each in its own part of LDS
+        const uint32_t m = d.v1 - d.v0, each = tile_lds_bytes(step_a, step_b, ES), rgs = (step_b + R - 1u) / R;
+        for (uint32_t i = tid; i < m * rgs << vl2; i += nthr) {
+            const uint32_t rr = i >> vl2, c = i & vmask, k = rr / rgs, b = (rr - k * rgs) * R;
+            const TileAt at = tile_offsets(d, d.v0 + k, ES);
+            const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
+            const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
+            if (b >= nb || c * V >= na) continue;
+            u32x4 x[R];
+#pragma unroll
+            for (uint32_t q = 0; q < R; ++q) {
+                const uint32_t r = b + q < nb ? b + q : nb - 1u;
+                x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
+            }
+            tile_put<ES, R>(lds + k * each, x, c * V, b, sp);
+        }
+        __syncthreads();
+        const uint32_t per = step_a * slots;
+        for (uint32_t i = tid; i < m * per; i += nthr) {
+            const uint32_t k = i / per, j = i - k * per;
+            const TileAt at = tile_offsets(d, d.v0 + k, ES);
+            const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
+            const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
+            const uint32_t aa = fastdiv(j, d.pad[1], tile_slot_shift(d)), b0 = (j - aa * slots) * V;
+            if (aa < na && b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds + k * each, sp, at.dst, nb, aa, b0);
+        }
     }
 }
 
-template <int NPTR>
+// FAN: 1 for one receiver (4 vectors per lane in flight), 2 for two and more
+// (one group), 4 for four and more, where 2-byte elements move one row at a
+// time: with two loads in flight their reads queue behind the writes (fp16
+// [8,2048,12288] to 4 receivers, 512-byte columns: 4, 2 and 1 in flight 402,
+// 376 and 369 us; at fan-out 2, bf16 in 224-byte columns, 1 is slower, 54.2
+// against 59.3 us).
+template <int NPTR, int ES, uint32_t FAN, bool PLAIN>
 __global__ __launch_bounds__(256) void reshard_transpose_kernel(KArgs<NPTR> args) {
     const RS_CONST KArgs<NPTR> *a = (const RS_CONST KArgs<NPTR> *)__builtin_amdgcn_kernarg_segment_ptr();
     const uint32_t b = blockIdx.x;
-    const uint32_t idx = a->per_xcd ? (b & 7u) * a->per_xcd + (b >> 3) : b;
+    uint32_t idx = b;
+    if (a->per_xcd) idx = (b & 7u) * a->per_xcd + (b >> 3);
+    else if (PLAIN) idx = (b / (8u * a->group)) * (8u * a->group) + (b & 7u) * a->group + (b >> 3) % a->group;
     if (idx >= a->ndesc) return;
     const Desc d = load_desc(a, idx);
-    if (d.nfan == 1) {
-        switch (d.kind & 0xFu) {
-            case 0: run_transpose<1, 4>(d, a); break;
-            case 1: run_transpose<2, 4>(d, a); break;
-            case 2: run_transpose<4, 4>(d, a); break;
-            default: run_transpose<8, 4>(d, a); break;
-        }
-    } else {
-        switch (d.kind & 0xFu) {
-            case 0: run_transpose<1, 1>(d, a); break;
-            case 1: run_transpose<2, 1>(d, a); break;
-            case 2: run_transpose<4, 1>(d, a); break;
-            default: run_transpose<8, 1>(d, a); break;
-        }
-    }
+    constexpr uint32_t R = ES == 1 ? 4u : ES == 2 && FAN < 4u ? 2u : 1u;
+    run_transpose<ES, R, (FAN == 1u ? 4u / R : 1u), PLAIN>(d, a);
 }
 
 // Unit-gather chunks in their own kernel, so the slot kernel keeps its
@@ -1302,7 +1370,7 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
     a.ndesc = 0;
     a.nsrc = uint32_t(p.src.ndev);
     a.per_xcd = 0;
-    a.pad = 0;
+    a.group = 1;
     for (int64_t k = 0; k < p.src.ndev; ++k) a.ptr[k] = src_ptrs[k];
     for (int64_t k = 0; k < p.dst.ndev; ++k) a.ptr[p.src.ndev + k] = dst_ptrs[k];
     const bool remap = (p.flags & RESHARD_XCD_REMAP) != 0;
@@ -1386,13 +1454,29 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         if (st != RESHARD_OK) return st;
     }
     if (n_transpose) {
-        // the widest tile of the plan (rows of kTileBytes) in LDS;
-        // no residency cap
+        // the largest tile of the plan in LDS; no residency cap
         a.descs = descs + n_direct + n_gather + n_gather_u;
         const uint32_t tblock = block < 256u ? block : 256u;
-        const uint32_t lds = p.transpose_rows * kTileBytes;
-        const reshard_status_t st =
-            launch_one(reshard_transpose_kernel<NPTR>, a, n_transpose, remap, tblock, lds, stream);
+        const uint32_t lds = std::max<uint32_t>(p.transpose_lds, n_transpose >= 4096u ? kTLeastLds : 0u);
+        a.group = p.transpose_plain ? std::max(1u, std::min<uint32_t>(kTGroup, n_transpose / 64u)) : 1u;
+        const auto go = [&](auto es, auto fan, auto plain) {
+            return launch_one(reshard_transpose_kernel<NPTR, decltype(es)::value, decltype(fan)::value, decltype(plain)::value>,
+                              a, n_transpose, remap, tblock, lds, stream, 8u * a.group);
+        };
+        const auto with_es = [&](auto plain) {
+            using I1 = std::integral_constant<uint32_t, 1>;
+            using I2 = std::integral_constant<uint32_t, 2>;
+            const bool one = p.max_fanout == 1;
+            switch (p.es) {
+                case 1: return one ? go(std::integral_constant<int, 1>{}, I1{}, plain) : go(std::integral_constant<int, 1>{}, I2{}, plain);
+                case 2:
+                    if (p.max_fanout >= 4) return go(std::integral_constant<int, 2>{}, std::integral_constant<uint32_t, 4>{}, plain);
+                    return one ? go(std::integral_constant<int, 2>{}, I1{}, plain) : go(std::integral_constant<int, 2>{}, I2{}, plain);
+                case 4: return one ? go(std::integral_constant<int, 4>{}, I1{}, plain) : go(std::integral_constant<int, 4>{}, I2{}, plain);
+                default: return one ? go(std::integral_constant<int, 8>{}, I1{}, plain) : go(std::integral_constant<int, 8>{}, I2{}, plain);
+            }
+        };
+        const reshard_status_t st = p.transpose_plain ? with_es(std::true_type{}) : with_es(std::false_type{});
         if (st != RESHARD_OK) return st;
     }
     if (n_realign) {

@@ -504,6 +504,10 @@ void split_emit(Plan &p, Piece pc, int32_t src_buf, int64_t fan_off, int64_t nfa
 #ifndef RS_TMAXW_LOG2
 #define RS_TMAXW_LOG2 2u  // widest tile along B: 4 x 128 bytes
 #endif
+constexpr int64_t kTilePart = 64;         // bytes memory writes as one (see emit_transpose)
+constexpr int64_t kTileGrow = 16384;      // bytes of a tile that is narrow along one extent, at most
+constexpr uint32_t kTileLds = 32768;      // LDS of a chunk's tiles, at most
+constexpr int64_t kTileMaxSide = 1024;    // ... and its other side, at most
 
 // Tile-transpose piece (see desc.h): A contiguous in the sender's buffer, B
 // in the receivers'; outer levels outermost first (any number: more than two
@@ -593,27 +597,72 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
     const int nl = int(tp.outer.size());
     const Level o1 = nl >= 1 ? tp.outer[size_t(nl - 1)] : Level{1, 0, 0};
     const Level o2 = nl >= 2 ? tp.outer[0] : Level{1, 0, 0};
-    // tile width along B: the narrowest of 1, 2, 4 x 128 bytes that covers
-    // the whole B extent (a tile then writes whole destination rows), with at
-    // most 256 tile rows (32 KiB of LDS); B extents wider than that take
-    // 2 x 128 bytes, which keeps twice the tiles resident (measured: 512-byte
-    // rows 382.6 us at 512-byte tiles against 391.6 at 256; 1 KiB rows 24.4
-    // against 26.2 us the other way).  With one receiver, 2 x 128 bytes at
-    // most (measured: workload 5's tensor to one replica, 512-byte rows,
-    // 150.5 us against 152.6 at 512-byte tiles; with 4 replicas 512-byte
-    // tiles stay ahead, 381.2 against 388.3).
-    uint32_t wide = 0;
-    while (wide < RS_TMAXW_LOG2 && (te << wide) < tp.nb && (te << (wide + 1)) <= 256) ++wide;
-    if (((te << wide) < tp.nb || nfan == 1) && wide > 1) wide = 1;
-    const int64_t tr = te << wide;
-    const uint64_t ntb = uint64_t((tp.nb + tr - 1) / tr), nta = uint64_t((tp.na + te - 1) / te);
-    const uint64_t tiles = ntb * nta * uint64_t(o1.n) * uint64_t(o2.n);
-    Desc d{};
     bool ald = tp.src_off % 16 == 0 && tp.ss_b % 16 == 0 && o1.ss % 16 == 0 && o2.ss % 16 == 0;
     bool ast = tp.dst_off % 16 == 0 && tp.ds_a % 16 == 0 && o1.ds % 16 == 0 && o2.ds % 16 == 0;
-    uint32_t log2es = 0;
+    // Tile extents in bytes, powers of two.  Along A one cache line.  Along
+    // B the narrowest of 1, 2, 4 lines that covers the whole B extent (a tile
+    // then writes whole destination rows), with at most 256 tile rows; B
+    // extents wider than that take 2 lines, which keeps twice the tiles
+    // resident (measured: 512-byte rows 382.6 us at 512-byte tiles against
+    // 391.6 at 256; 1 KiB rows 24.4 against 26.2 us the other way).  With one
+    // receiver, 2 lines at most (measured: workload 5's tensor to one
+    // replica, 512-byte rows, 150.5 us against 152.6 at 512-byte tiles; with
+    // 4 replicas 512-byte tiles stay ahead, 381.2 against 388.3).
+    // Where one extent is under a line, the tile is as narrow as it there
+    // and up to kTileGrow bytes in all along the other.
+    const int64_t rowb = tp.na * es, colb = tp.nb * es;
+    const int64_t grow = std::min<int64_t>(kTileGrow, chunk_bytes);
+    int64_t wa = kTileBytes, wb = kTileBytes;
+    while (wb < (int64_t(kTileBytes) << RS_TMAXW_LOG2) && wb < colb && wb * 2 <= 256 * es) wb *= 2;
+    if ((wb < colb || nfan == 1) && wb > 2 * int64_t(kTileBytes)) wb = 2 * int64_t(kTileBytes);
+    while (wa / 2 >= std::max<int64_t>(rowb, 16)) wa /= 2;
+    while (wb / 2 >= std::max<int64_t>(colb, 16)) wb /= 2;
+    if (wa < int64_t(kTileBytes))
+        while (wb < colb && wb < kTileMaxSide && wa * wb * 2 / es <= grow) wb *= 2;
+    if (wb < int64_t(kTileBytes))
+        while (wa < rowb && wa < kTileMaxSide && wa * wb * 2 / es <= grow) wa *= 2;
+    // Small tensors take smaller tiles (4 KiB and more), for 512 of them:
+    // 32 KiB tiles left CUs idle (bf16 [39,144,128] to 8 receivers 8.0 ->
+    // 5.5 us; uint8 [8,176,768] to 4 6.6 -> 4.6 us).
+    const int64_t tgt = std::max<int64_t>(4096, p.bytes_read / 512);
+    while (wa * wb / es > tgt) {
+        if (wb > int64_t(kTileBytes)) wb /= 2;
+        else if (wa > int64_t(kTileBytes) / 2) wa /= 2;
+        else break;
+    }
+    // Tiles along an extent are equal, in whole vectors on a side whose rows
+    // start on 16-byte boundaries (whole tiles where there are many).
+    auto step_of = [&](int64_t n, int64_t w, bool aligned) {
+        const int64_t we = w / es, v = 16 / es, k = (n + we - 1) / we;
+        if (k <= 1) return std::min(n, we);
+        if (aligned && k > 4) return we;
+        const int64_t st = (n + k - 1) / k;
+        return aligned ? (st + v - 1) / v * v : st;
+    };
+    const int64_t ta = step_of(tp.na, wa, ald), tr = step_of(tp.nb, wb, ast);
+    const uint64_t ntb = uint64_t((tp.nb + tr - 1) / tr), nta = uint64_t((tp.na + ta - 1) / ta);
+    const uint64_t tiles = ntb * nta * uint64_t(o1.n) * uint64_t(o2.n);
+    Desc d{};
+    uint32_t log2es = 0, vl2 = 0;
     while ((int64_t(1) << log2es) < es) ++log2es;
-    d.kind = uint8_t(log2es | (ald ? kTAlignLoad : 0u) | (ast ? kTAlignStore : 0u) | (wide << 6));
+    while ((int64_t(16) << vl2) < ta * es) ++vl2;
+    d.kind = uint8_t(log2es);
+    // Tiles that write parts of 64-byte groups take the kernel's plain
+    // stores; whole ones are best non-temporal, whole cache lines or not
+    // (fp16 [16,1088,3328], two 1088-byte halves of each column, to 4
+    // receivers: 122 us non-temporal, 143 plain; 1056-byte halves, not whole
+    // groups: 204 and 159).  Where columns follow one another in the buffer,
+    // a tile's bytes are one run, with two parts in all: not counted from
+    // 2 KiB on (fp16 [12,48,11008] to 4 receivers, 96-byte columns: 11.2 us
+    // non-temporal, 13.3 plain).
+    const bool dense = tr == tp.nb && tp.ds_a == tp.nb * es && ta * tp.nb * es >= 2048;
+    p.transpose_plain = p.transpose_plain ||
+                        (!dense && (tp.dst_off % kTilePart || tp.ds_a % kTilePart || o1.ds % kTilePart || o2.ds % kTilePart ||
+                                    tr * es % kTilePart));
+    const FastDiv fsl = make_fastdiv(uint32_t((tr * es + 15) / 16));
+    d.pad[0] = vl2 | (fsl.shift << 8);
+    d.pad[1] = fsl.mul;
+    d.pad[2] = uint32_t(ta) | (uint32_t(tr) << 16);
     d.ss[0] = uint32_t(uint64_t(tp.ss_b));
     d.ds[0] = uint32_t(uint64_t(tp.ds_a));
     d.ss[1] = uint32_t(uint64_t(o1.ss));
@@ -632,7 +681,11 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
     d.src_buf = uint16_t(src_buf);
     d.nfan = uint16_t(nfan);
     d.fan_off = uint32_t(fan_off);
-    const uint64_t per = uint64_t(std::max<int64_t>(1, chunk_bytes / (te * tr * es)));
+    const uint32_t each = tile_lds_bytes(uint32_t(ta), uint32_t(tr), uint32_t(es));
+    // Tiles per chunk: one, or as many small ones (up to half a chunk each)
+    // as fill it, which its workgroup moves at once.
+    const uint64_t per = std::max<uint64_t>(
+        1, std::min(uint64_t(chunk_bytes / (ta * tr * es)), uint64_t(kTileLds / each)));
     if (p.descs.size() + out.size() + (tiles + per - 1) / per > kMaxDescs) {
         p.too_many = true;
         return;
@@ -649,7 +702,7 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
         t0 = t1;
     }
     p.align = std::max<int64_t>(p.align, (ald || ast) ? 16 : es);
-    p.transpose_rows = std::max(p.transpose_rows, uint32_t(tr));
+    p.transpose_lds = std::max(p.transpose_lds, uint32_t(std::min(per, tiles)) * each);
 }
 
 int64_t auto_chunk_bytes(int64_t bytes_read) {
@@ -1124,7 +1177,8 @@ void lower(Plan &p) {
     p.fan.assign(p.dst.shard_devs.begin(), p.dst.shard_devs.end());
     p.align = 1;
     p.lds_bytes = 0;
-    p.transpose_rows = 0;
+    p.transpose_lds = 0;
+    p.transpose_plain = false;
     p.too_many = false;
     p.tile_span_too_long = false;
     p.max_fanout = 0;

@@ -83,7 +83,8 @@ struct Plan {
     size_t n_gather_u = 0;     // then n_gather_u unaligned row-gather chunks (the last n_unit
     size_t n_unit = 0;         // of them unit-gather chunks, their own kernel);
     size_t n_transpose = 0;    // then n_transpose tile-transpose chunks;
-    uint32_t transpose_rows = 0;  // rows of the widest transpose tile (LDS: rows x 128 bytes)
+    bool transpose_plain = false;  // some transpose tiles write parts of cache lines
+    uint32_t transpose_lds = 0;  // LDS bytes of the largest transpose tile
                                // the rest: realignment chunks
     std::vector<Seg> segs;     // row-gather segment entries
     int64_t gather_fanout = 0; // largest receiver count among row-gather chunks

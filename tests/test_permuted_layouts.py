@@ -102,6 +102,25 @@ def test_host_transpose_unaligned_rows():
         assert B.reshard_plan_transpose_chunks(p) > 0
 
 
+# extents at the edges of the transpose's tiles: rows or columns under 16
+# bytes, one element past a tile, a last tile narrower than a vector, tiles
+# that grow along one side, many small tiles in one chunk, columns on and off
+# cache lines; (shape, bytes per element)
+TILE_EDGES = [((3, 700), 1), ((700, 3), 1), ((9, 5, 7), 2), ((40, 9, 11), 8), ((2, 65, 513), 2), ((2, 513, 65), 2),
+              ((1, 17, 4100), 1), ((1, 4100, 17), 1), ((1, 48, 2080), 2), ((300, 12, 20), 4), ((1, 2050, 2056), 2),
+              ((1, 257, 1029), 1), ((1, 1031, 1040), 4)]
+_TILE_DT = {1: "uint8", 2: "float16", 4: "float32", 8: "float64"}
+
+
+@pytest.mark.parametrize("fan", [1, 3])
+@pytest.mark.parametrize("shape,es", TILE_EDGES)
+def test_host_transpose_tile_edges(shape, es, fan):
+    nd = len(shape)
+    dp = tuple(range(nd - 2)) + (nd - 1, nd - 2)
+    p = host_perm_case(shape, _TILE_DT[es], (2,), "R" * (nd - 1) + "S^0", None, (fan, 2), "R" * (nd - 2) + "S^1R", dp)
+    assert B.reshard_plan_transpose_chunks(p) > 0
+
+
 def test_permuted_outer_dims_need_no_transpose():
     # same innermost dimension on both sides, outer dimensions swapped: the
     # direct path with per-side strides, no tile transposes
@@ -209,6 +228,17 @@ def test_gpu_transpose_tiles(dt, shape):
     dp = tuple(range(nd - 2)) + (nd - 1, nd - 2)
     print(f"transpose tiles {dt} {shape}", flush=True)
     p = _gpu_run(shape, dt, (2,), "S^0" + "R" * (nd - 1), None, (2,), "R" * nd, dp)
+    assert B.reshard_plan_transpose_chunks(p) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fan", [1, 3])
+@pytest.mark.parametrize("shape,es", TILE_EDGES)
+def test_gpu_transpose_tile_edges(shape, es, fan):
+    nd = len(shape)
+    dp = tuple(range(nd - 2)) + (nd - 1, nd - 2)
+    print(f"transpose tile edges {shape} es={es} fan={fan}", flush=True)
+    p = _gpu_run(shape, _TILE_DT[es], (2,), "R" * (nd - 1) + "S^0", None, (fan, 2), "R" * (nd - 2) + "S^1R", dp)
     assert B.reshard_plan_transpose_chunks(p) > 0
 
 
