@@ -121,6 +121,28 @@ def test_host_transpose_tile_edges(shape, es, fan):
     assert B.reshard_plan_transpose_chunks(p) > 0
 
 
+# [batch, seq, head, dim] to [batch, head, seq, dim] and back, in blocks: the
+# last block of a head short or whole, blocks wider than the rows left, rows
+# a multiple of 4 KiB apart (the receiver sets take turns) and not, one batch
+HEADS = [((2, 80, 32, 64), "float16", (2,), (2, 2)), ((2, 64, 32, 64), "float16", (2,), (1, 4)),
+         ((3, 70, 10, 40), "float16", (2,), (2, 2)), ((1, 300, 7, 16), "float32", (1,), (1, 2)),
+         ((2, 33, 16, 64), "float16", (1,), (3, 2)), ((2, 130, 8, 128), "uint8", (2,), (1, 4))]
+
+
+def heads_case(run, shape, dt, sm, dm, back):
+    a, b = "RS^0RR", "RRS^1R"
+    if back:
+        return run(shape, dt, dm, b, (0, 2, 1, 3), sm, a, None)
+    return run(shape, dt, sm, a, None, dm, b, (0, 2, 1, 3))
+
+
+@pytest.mark.parametrize("back", [False, True])
+@pytest.mark.parametrize("shape,dt,sm,dm", HEADS)
+def test_host_heads(shape, dt, sm, dm, back):
+    p = heads_case(host_perm_case, shape, dt, sm, dm, back)
+    assert B.reshard_plan_transpose_chunks(p) == 0
+
+
 def test_permuted_outer_dims_need_no_transpose():
     # same innermost dimension on both sides, outer dimensions swapped: the
     # direct path with per-side strides, no tile transposes
@@ -240,6 +262,14 @@ def test_gpu_transpose_tile_edges(shape, es, fan):
     print(f"transpose tile edges {shape} es={es} fan={fan}", flush=True)
     p = _gpu_run(shape, _TILE_DT[es], (2,), "R" * (nd - 1) + "S^0", None, (fan, 2), "R" * (nd - 2) + "S^1R", dp)
     assert B.reshard_plan_transpose_chunks(p) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("back", [False, True])
+@pytest.mark.parametrize("shape,dt,sm,dm", HEADS)
+def test_gpu_heads(shape, dt, sm, dm, back):
+    print(f"heads {shape} {dt} {sm} {dm} back={back}", flush=True)
+    heads_case(_gpu_run, shape, dt, sm, dm, back)
 
 
 @pytest.mark.gpu
