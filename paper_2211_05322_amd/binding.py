@@ -223,6 +223,10 @@ def reshard_plan(shape, dtype, src_mesh, src_spec, dst_mesh, dst_spec, flags=0,
 def _stream_handle(stream):
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            # the handle alone: torch.cuda.current_stream() builds a Stream
+            # object around it, 2.7 us of a call's 7 (0.2 us this way)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -242,8 +246,9 @@ def reshard_execute(plan, src_bufs, dst_bufs, stream=None):
     """
     if len(src_bufs) != plan.n_src or len(dst_bufs) != plan.n_dst:
         raise ValueError(f"need {plan.n_src} source and {plan.n_dst} destination buffers")
-    _check(load().reshard_execute(plan.handle, _ptrs(src_bufs), _ptrs(dst_bufs),
-                                  ctypes.c_void_p(_stream_handle(stream))))
+    status = (_lib or load()).reshard_execute(plan._h, _ptrs(src_bufs), _ptrs(dst_bufs), _stream_handle(stream))
+    if status != RESHARD_OK:
+        _check(status)
 
 
 def reshard_execute_noalloc(plan, src_bufs, dst_bufs, stream=None):
@@ -252,8 +257,10 @@ def reshard_execute_noalloc(plan, src_bufs, dst_bufs, stream=None):
     and for calls that overlap)."""
     if len(src_bufs) != plan.n_src or len(dst_bufs) != plan.n_dst:
         raise ValueError(f"need {plan.n_src} source and {plan.n_dst} destination buffers")
-    _check(load().reshard_execute_noalloc(plan.handle, _ptrs(src_bufs), _ptrs(dst_bufs),
-                                          ctypes.c_void_p(_stream_handle(stream))))
+    status = (_lib or load()).reshard_execute_noalloc(plan._h, _ptrs(src_bufs), _ptrs(dst_bufs),
+                                                      _stream_handle(stream))
+    if status != RESHARD_OK:
+        _check(status)
 
 
 def reshard_debug_execute_host(plan, src_bufs, dst_bufs):

@@ -1338,9 +1338,15 @@ reshard_status_t launch_one(K kernel, A a, uint32_t ndesc, bool remap, uint32_t 
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
         if (ea != hipSuccess) return hip_fail("raising the kernel's LDS limit", ea);
     }
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds, stream, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail("kernel launch", e);
+    // launched without the <<<>>> stub and its thread-local launch
+    // configuration (0.2 us of a call's 4.0)
+    void *argv[] = {&a};
+    const hipError_t e =
+        hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block), argv, lds, stream);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return hip_fail("kernel launch", e);
+    }
     return RESHARD_OK;
 }
 

@@ -623,3 +623,22 @@ def test_other_element_types(dt):
         _say(f"dtype {dt} {shape}")
         got, want = run_gpu(shape, dt, sm, ss, dm, ds, rand_bits(shape, dt, 31))
         assert_same(got, want)
+
+
+def test_default_stream_is_torchs_current_one():
+    """Without a stream argument the call runs on torch's current stream:
+    the default one, another one, and the one a graph is captured on."""
+    def same():
+        assert B._stream_handle(None) == torch.cuda.current_stream().cuda_stream
+    same()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        same()
+        assert B._stream_handle(None) == s.cuda_stream
+    same()
+    g = torch.cuda.CUDAGraph()
+    x = torch.zeros(4, device="cuda")
+    with torch.cuda.graph(g):
+        same()
+        x.add_(1)
+    same()
