@@ -1393,8 +1393,18 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
     // 64 receiver write streams per CU (64 / fan-out waves, at least 8).
     const uint32_t user_lds =
         p.tuning.max_wgs_per_cu ? lds_for_per_half(uint32_t(p.tuning.max_wgs_per_cu) / 2u) : 0u;
+    // Those caps are for reshards that stream through HBM.  One whose bytes,
+    // read and written, fit in the last-level cache is bound by latency and
+    // runs with 32 waves per CU (none of its buffers cached before, same
+    // machine, us, capped -> 32 waves: direct fp16 [29,32,10304] to 4
+    // receivers, 96 MB, 26.5 -> 17.8, fp32 [22,192,16,64] to 2, 52 MB, 17.9
+    // -> 13.7; gather fp32 [8,2272,192] to 8, 126 MB, 28.4 -> 22.7; slots
+    // bf16 [10,2157,626] to 4, 135 MB, 42.9 -> 27.0; at 196-279 MB 1.15 to
+    // 1.27 times as fast; past that the caps lead, 52.6 against 59.1 direct
+    // at 315 MB, 215 against 247 slots at 1.1 GB).
+    const bool cached = p.bytes_read + p.bytes_written <= int64_t(256) << 20;
     const uint32_t cap_lds =
-        p.tuning.cap_is_default ? residency_lds(p.direct_fanout <= 2 ? 16u : 8u, dblock) : user_lds;
+        p.tuning.cap_is_default ? residency_lds(cached ? 32u : p.direct_fanout <= 2 ? 16u : 8u, dblock) : user_lds;
     const uint32_t n_direct = uint32_t(p.n_direct), n_gather = uint32_t(p.n_gather);
     const uint32_t n_gather_u = uint32_t(p.n_gather_u);
     const uint32_t n_transpose = uint32_t(p.n_transpose);
@@ -1414,7 +1424,7 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         uint32_t gcap_lds = user_lds;
         if (p.tuning.cap_is_default) {
             const uint32_t fan = uint32_t(p.gather_fanout > 0 ? p.gather_fanout : 1);
-            gcap_lds = residency_lds(64u / fan > 8u ? 64u / fan : 8u, block);
+            gcap_lds = residency_lds(cached ? 32u : 64u / fan > 8u ? 64u / fan : 8u, block);
         }
         const uint32_t need = (12u + 8u) * kMaxSegs;
         const uint32_t glds = gcap_lds > need ? gcap_lds : need;
@@ -1438,7 +1448,7 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         const uint32_t fan = uint32_t(fanout > 0 ? fanout : 1);
         uint32_t waves = 64u / fan > 8u ? 64u / fan : 8u;
         if (segs == 1) waves = fan <= 1 ? 32u : fan == 2 ? 16u : 8u;
-        if (more_waves && waves < 32u) waves = 32u;
+        if ((more_waves || cached) && waves < 32u) waves = 32u;
         return residency_lds(waves, block < 256u ? block : 256u);
     };
     if (n_slot) {
