@@ -126,7 +126,7 @@ static_assert(sizeof(Desc) == 112, "descriptor layout is shared by host and devi
 // alignment).
 //
 // Unit gather (kind | kUnitGather, in the unaligned row-gather section, for
-// one receiver): lanes take 16-byte units of each segment's row rather than
+// one receiver or two): lanes take 16-byte units of each segment's row rather than
 // slots of the destination -- unit k of a segment of width w covers bytes
 // [min(16k, w - 16), +16), so the last unit overlaps the one before it and
 // rewrites the same bytes -- each one unaligned 16-byte load and one

@@ -966,6 +966,7 @@ void halve_gather_tail(std::vector<Desc> &g, size_t k) {
 #ifndef RS_UNIT_MAX_SEG
 #define RS_UNIT_MAX_SEG 2048  // the unit gather takes mean segment widths below this (bytes)
 #endif
+constexpr int64_t kUnitRow2 = 8192;  // ... and rows below this to two receivers from one sender
 
 // Unaligned row gather of one group (see desc.h): segments of any widths
 // tiling the destination row (one segment per row too, when its rows are in
@@ -1123,9 +1124,13 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
     // The slot form spends its time on slots that straddle two segments
     // (or rows), which short segments make frequent.  Measured against
     // destination slots: 8 % faster with 770-byte segments at fan-out 1, 18 %
-    // with 4-byte segments among them; slower at fan-out 2 and with rows of
-    // 6 KiB and more from one sender.
-    bool unit = nfan <= int64_t(RS_UNIT_MAX_FAN) && row_bytes < int64_t(RS_UNIT_MAX_SEG) * int64_t(ns);
+    // with 4-byte segments among them; slower with rows of 6 KiB and more
+    // from one sender.  Two receivers gain too where a row has one sender, up
+    // to kUnitRow2 bytes (uint8 [64,1025,1001] by 250-byte rows 42.9 -> 38.2
+    // us, 1500-byte rows 262 -> 253, 7000-byte rows 16.2 -> 15.1); with 32
+    // senders per row they lose (228 -> 249), as do 4 receivers and more.
+    const int64_t seg_mean_limit = nfan == 2 && ns == 1 ? kUnitRow2 : int64_t(RS_UNIT_MAX_SEG) * int64_t(ns);
+    bool unit = (nfan <= int64_t(RS_UNIT_MAX_FAN) || (nfan == 2 && ns == 1)) && row_bytes < seg_mean_limit;
     uint32_t upr = 0;  // units per row
     bool unit_short = false;
     for (size_t k = 0; k < ns; ++k) {

@@ -555,6 +555,26 @@ def test_short_segments_take_units_at_fanout_one(case):
     assert (B.reshard_plan_unit_gather_chunks(p) > 0) == (fanout == 1), fanout
 
 
+# one sender per row to two receivers: rows of 15 to 17 bytes, odd rows, the
+# last row under the unit gather's 8 KiB and the first above it; (case, units)
+UNIT_PAIR_CASES = [
+    (((4, 70, 30), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), True),     # 15-byte rows: units under 16 bytes
+    (((4, 70, 34), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), True),     # 17-byte rows
+    (((6, 33, 1001), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), True),   # 251/250-byte rows in runs
+    (((3, 5, 8194), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # 8194-byte rows
+    (((3, 5, 8190), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), True),  # 8190-byte rows
+]
+
+
+@pytest.mark.parametrize("chunk", [0, 256])
+@pytest.mark.parametrize("case,units", UNIT_PAIR_CASES)
+def test_host_units_to_two_receivers(case, units, chunk):
+    p = plan_of(*case, chunk_bytes=chunk)
+    assert B.reshard_plan_unaligned_gather_chunks(p) > 0
+    assert (B.reshard_plan_unit_gather_chunks(p) > 0) == units
+    host_case(*case, chunk_bytes=chunk)
+
+
 def test_gather_used_by_column_split_workloads():
     for wid, w in WORKLOADS.items():
         p = plan_of(w.shape, w.dtype, w.src_mesh, w.src_spec, w.dst_mesh, w.dst_spec)

@@ -385,7 +385,16 @@ def test_unaligned_gather_chunk_counts_around_xcd_runs(shape, n, dm):
         assert_same(got, want)
 
 
-from tests.test_capi_host import RUN_CASES  # noqa: E402
+from tests.test_capi_host import RUN_CASES, UNIT_PAIR_CASES  # noqa: E402
+
+
+@pytest.mark.parametrize("case,units", UNIT_PAIR_CASES)
+def test_units_to_two_receivers(case, units):
+    shape, dt, sm, ss, dm, ds = case
+    for kw in ({}, {"chunk_bytes": 256, "block_threads": 64}):
+        _say(f"units to two receivers {case} {kw}")
+        got, want = run_gpu(shape, dt, sm, ss, dm, ds, rand_bits(shape, dt, 29), **kw)
+        assert_same(got, want)
 
 
 @pytest.mark.parametrize("case", RUN_CASES)
