@@ -361,7 +361,7 @@ reshard_status_t reshard_debug_execute_host(const reshard_plan_t *plan, void *co
                     return fail(RESHARD_EINVAL, "internal: transpose tile extents");
                 const uint64_t sbytes = uint64_t(p->src_local_numel[d.src_buf] * p->es);
                 const uint32_t each = rs::tile_lds_bytes(step_a, step_b, es);
-                if (uint64_t(each) * (d.v1 - d.v0) > p->transpose_lds)
+                if (uint64_t(each) * std::min(d.v1 - d.v0, rs::tiles_at_once(each)) > p->transpose_lds)
                     return fail(RESHARD_EINVAL, "internal: transpose tiles larger than their LDS");
                 lds.assign(each, 0);
                 auto out = [&](uint64_t off, const uint8_t *y, uint32_t n) {

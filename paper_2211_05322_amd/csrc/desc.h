@@ -200,7 +200,7 @@ constexpr TileAt tile_offsets(const Desc &d, uint32_t t, uint32_t es) {
 // tile make one 16-byte slot of it) at a * tile_col_bytes, its slot j at slot
 // j ^ tile_swizzle(a): the load phase writes dwords of 16 / es neighbouring
 // columns (and 8 neighbouring vectors) at once, which the exchange spreads
-// over the banks.   Columns are counted in whole
+// over the banks.  Columns are counted in whole
 // vectors of rows.
 constexpr uint32_t tile_slots_padded(uint32_t slots) {
     return slots > 4u ? (slots + 7u) & ~7u : slots > 2u ? 4u : slots;
@@ -211,6 +211,11 @@ constexpr uint32_t tile_swizzle(uint32_t a, uint32_t slots_padded, uint32_t es) 
 constexpr uint32_t tile_lds_bytes(uint32_t step_a, uint32_t step_b, uint32_t es) {
     return (step_a * es + 15u) / 16u * (16u / es) * 16u * tile_slots_padded((step_b * es + 15u) / 16u);
 }
+// Tiles of a chunk that its workgroup holds in LDS at once, each in a part of
+// its own; a chunk of more (only where chunk_bytes is over kTileLds) goes
+// through them so many at a time.
+constexpr uint32_t kTileLds = 32768;
+constexpr uint32_t tiles_at_once(uint32_t each) { return each < kTileLds ? kTileLds / each : 1u; }
 
 // Outer-level indices of a row (level 1 = innermost outer level).
 template <int LEVELS>

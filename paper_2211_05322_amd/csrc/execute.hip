@@ -1179,31 +1179,36 @@ __device__ __forceinline__ void run_transpose(const Desc &d, const RS_CONST KArg
             if (b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds, sp, at.dst, nb, aa, b0);
         }
     } else {
-        // small tiles, all of the chunk at once, each in its own part of LDS
-        const uint32_t m = d.v1 - d.v0, each = tile_lds_bytes(step_a, step_b, ES), rgs = (step_b + R - 1u) / R;
-        for (uint32_t i = tid; i < m * rgs << vl2; i += nthr) {
-            const uint32_t rr = i >> vl2, c = i & vmask, k = rr / rgs, b = (rr - k * rgs) * R;
-            const TileAt at = tile_offsets(d, d.v0 + k, ES);
-            const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
-            const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
-            if (b >= nb || c * V >= na) continue;
-            u32x4 x[R];
+        // small tiles, as many at once as LDS takes (by default all of the
+        // chunk), each in its own part of it
+        const uint32_t each = tile_lds_bytes(step_a, step_b, ES), rgs = (step_b + R - 1u) / R;
+        const uint32_t once = tiles_at_once(each), per = step_a * slots;
+        for (uint32_t t0 = d.v0, m; t0 < d.v1; t0 += m) {
+            m = d.v1 - t0 < once ? d.v1 - t0 : once;
+            for (uint32_t i = tid; i < m * rgs << vl2; i += nthr) {
+                const uint32_t rr = i >> vl2, c = i & vmask, k = rr / rgs, b = (rr - k * rgs) * R;
+                const TileAt at = tile_offsets(d, t0 + k, ES);
+                const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
+                const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
+                if (b >= nb || c * V >= na) continue;
+                u32x4 x[R];
 #pragma unroll
-            for (uint32_t q = 0; q < R; ++q) {
-                const uint32_t r = b + q < nb ? b + q : nb - 1u;
-                x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
+                for (uint32_t q = 0; q < R; ++q) {
+                    const uint32_t r = b + q < nb ? b + q : nb - 1u;
+                    x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
+                }
+                tile_put<ES, R>(lds + k * each, x, c * V, b, sp);
             }
-            tile_put<ES, R>(lds + k * each, x, c * V, b, sp);
-        }
-        __syncthreads();
-        const uint32_t per = step_a * slots;
-        for (uint32_t i = tid; i < m * per; i += nthr) {
-            const uint32_t k = i / per, j = i - k * per;
-            const TileAt at = tile_offsets(d, d.v0 + k, ES);
-            const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
-            const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
-            const uint32_t aa = fastdiv(j, d.pad[1], tile_slot_shift(d)), b0 = (j - aa * slots) * V;
-            if (aa < na && b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds + k * each, sp, at.dst, nb, aa, b0);
+            __syncthreads();
+            for (uint32_t i = tid; i < m * per; i += nthr) {
+                const uint32_t k = i / per, j = i - k * per;
+                const TileAt at = tile_offsets(d, t0 + k, ES);
+                const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
+                const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
+                const uint32_t aa = fastdiv(j, d.pad[1], tile_slot_shift(d)), b0 = (j - aa * slots) * V;
+                if (aa < na && b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds + k * each, sp, at.dst, nb, aa, b0);
+            }
+            if (d.v1 - t0 > m) __syncthreads();  // LDS is read before the next tiles are written
         }
     }
 }

@@ -553,7 +553,6 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
 #endif
 constexpr int64_t kTilePart = 64;         // bytes memory writes as one (see emit_transpose)
 constexpr int64_t kTileGrow = 16384;      // bytes of a tile that is narrow along one extent, at most
-constexpr uint32_t kTileLds = 32768;      // LDS of a chunk's tiles, at most
 constexpr int64_t kTileMaxSide = 1024;    // ... and its other side, at most
 
 // Tile-transpose piece (see desc.h): A contiguous in the sender's buffer, B
@@ -730,9 +729,11 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
     d.fan_off = uint32_t(fan_off);
     const uint32_t each = tile_lds_bytes(uint32_t(ta), uint32_t(tr), uint32_t(es));
     // Tiles per chunk: one, or as many small ones (up to half a chunk each)
-    // as fill it, which its workgroup moves at once.
-    const uint64_t per = std::max<uint64_t>(
-        1, std::min(uint64_t(chunk_bytes / (ta * tr * es)), uint64_t(kTileLds / each)));
+    // as fill it, which its workgroup moves at once.  Chunks larger than LDS
+    // takes at once (asked for, or a table that would be too long otherwise)
+    // loop over their tiles.
+    const uint64_t fill = uint64_t(chunk_bytes / (ta * tr * es)), once = tiles_at_once(each);
+    const uint64_t per = std::max<uint64_t>(1, chunk_bytes > int64_t(kTileLds) ? fill : std::min(fill, once));
     if (p.descs.size() + out.size() + (tiles + per - 1) / per > kMaxDescs) {
         p.too_many = true;
         return;
@@ -749,7 +750,7 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
         t0 = t1;
     }
     p.align = std::max<int64_t>(p.align, (ald || ast) ? 16 : es);
-    p.transpose_lds = std::max(p.transpose_lds, uint32_t(std::min(per, tiles)) * each);
+    p.transpose_lds = std::max(p.transpose_lds, uint32_t(std::min({per, tiles, once})) * each);
 }
 
 int64_t auto_chunk_bytes(int64_t bytes_read) {

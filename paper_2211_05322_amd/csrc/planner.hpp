@@ -83,10 +83,10 @@ struct Plan {
     size_t n_gather_u = 0;     // then n_gather_u unaligned row-gather chunks (the last n_unit
     size_t n_unit = 0;         // of them unit-gather chunks, their own kernel);
     size_t n_transpose = 0;    // then n_transpose tile-transpose chunks;
-    size_t n_spread = 0;       // direct chunks whose receiver sets share sender rows (chunk order)
-    bool transpose_plain = false;  // some transpose tiles write parts of cache lines
-    uint32_t transpose_lds = 0;  // LDS bytes of the largest transpose tile
                                // the rest: realignment chunks
+    size_t n_spread = 0;       // direct chunks whose receiver sets share sender rows (chunk order)
+    bool transpose_plain = false;  // some transpose tiles write parts of 64-byte groups
+    uint32_t transpose_lds = 0;  // LDS bytes of the largest set of tiles moved at once
     std::vector<Seg> segs;     // row-gather segment entries
     int64_t gather_fanout = 0; // largest receiver count among row-gather chunks
     int64_t gather_u_fanout = 0; // ... among unaligned row-gather chunks

@@ -121,6 +121,23 @@ def test_host_transpose_tile_edges(shape, es, fan):
     assert B.reshard_plan_transpose_chunks(p) > 0
 
 
+# chunks larger than LDS takes at once loop over their tiles
+TILE_LOOPS = [((1, 520, 1040), 2), ((300, 12, 20), 4), ((40, 9, 11), 8), ((1, 1030, 1290), 1)]
+
+
+@pytest.mark.parametrize("fan", [1, 4])
+@pytest.mark.parametrize("shape,es", TILE_LOOPS)
+def test_host_transpose_chunks_of_many_tiles(shape, es, fan):
+    p = host_perm_case(shape, _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1), chunk_bytes=1 << 17)
+    assert 0 < B.reshard_plan_transpose_chunks(p) <= -(-4 * shape[0] * shape[1] * shape[2] * es // (1 << 17))
+
+
+def test_transpose_table_follows_the_chunk_size():
+    # 64 GiB in 256 KiB chunks: 2^18 of them, not one per LDS load
+    p = B.reshard_plan((1, 1 << 16, 1 << 20), "uint8", (1,), "RRR", (1,), "RRR", dst_perm=(0, 2, 1), chunk_bytes=1 << 18)
+    assert B.reshard_plan_transpose_chunks(p) == 1 << 18
+
+
 # [batch, seq, head, dim] to [batch, head, seq, dim] and back, in blocks: the
 # last block of a head short or whole, blocks wider than the rows left, rows
 # a multiple of 4 KiB apart (the receiver sets take turns) and not, one batch
@@ -262,6 +279,14 @@ def test_gpu_transpose_tile_edges(shape, es, fan):
     print(f"transpose tile edges {shape} es={es} fan={fan}", flush=True)
     p = _gpu_run(shape, _TILE_DT[es], (2,), "R" * (nd - 1) + "S^0", None, (fan, 2), "R" * (nd - 2) + "S^1R", dp)
     assert B.reshard_plan_transpose_chunks(p) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fan", [1, 4])
+@pytest.mark.parametrize("shape,es", TILE_LOOPS)
+def test_gpu_transpose_chunks_of_many_tiles(shape, es, fan):
+    print(f"transpose chunks of many tiles {shape} es={es} fan={fan}", flush=True)
+    _gpu_run(shape, _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1), chunk_bytes=1 << 17)
 
 
 @pytest.mark.gpu
