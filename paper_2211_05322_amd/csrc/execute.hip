@@ -1406,10 +1406,16 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
     // -> 13.7; gather fp32 [8,2272,192] to 8, 126 MB, 28.4 -> 22.7; slots
     // bf16 [10,2157,626] to 4, 135 MB, 42.9 -> 27.0; at 196-279 MB 1.15 to
     // 1.27 times as fast; past that the caps lead, 52.6 against 59.1 direct
-    // at 315 MB, 215 against 247 slots at 1.1 GB).
-    const bool cached = p.bytes_read + p.bytes_written <= int64_t(256) << 20;
+    // at 315 MB, 215 against 247 slots at 1.1 GB).  Direct chunks to one
+    // receiver, half of whose bytes are reads, turn earlier (fp16
+    // [n,1024,4096] in three layouts, cold, 16 -> 32 waves: 101 MB 20.1 ->
+    // 19.6, 117 MB 23.0 -> 22.4, 134 MB 25.8 -> 26.1, 201 MB 36.5 -> 37.4,
+    // 252 MB 44.7 -> 45.6).
+    const int64_t bytes = p.bytes_read + p.bytes_written;
+    const bool cached = bytes <= int64_t(256) << 20;
+    const bool dcached = p.direct_fanout == 1 ? bytes <= int64_t(120) << 20 : cached;
     const uint32_t cap_lds =
-        p.tuning.cap_is_default ? residency_lds(cached ? 32u : p.direct_fanout <= 2 ? 16u : 8u, dblock) : user_lds;
+        p.tuning.cap_is_default ? residency_lds(dcached ? 32u : p.direct_fanout <= 2 ? 16u : 8u, dblock) : user_lds;
     const uint32_t n_direct = uint32_t(p.n_direct), n_gather = uint32_t(p.n_gather);
     const uint32_t n_gather_u = uint32_t(p.n_gather_u);
     const uint32_t n_transpose = uint32_t(p.n_transpose);
