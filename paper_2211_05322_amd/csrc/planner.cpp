@@ -517,6 +517,7 @@ constexpr int64_t kBlockBytes = 4096;
 
 void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int64_t nfan, int64_t chunk_bytes) {
     const size_t nl = pc.outer.size(), before = p.descs.size();
+    const bool had_too_many = p.too_many;
     size_t is = nl;
     for (size_t i = 0; i + 1 < nl; ++i)
         if (pc.outer[i].ss == pc.run) is = i;
@@ -543,6 +544,12 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
         rest.src_off += uint64_t(k * T * ld.ss);
         rest.dst_off += uint64_t(k * T * ld.ds);
         split_emit(p, rest, src_buf, fan_off, nfan, chunk_bytes);
+    }
+    if (p.too_many && !had_too_many) {  // the cuts cost the table its room: plain order
+        p.too_many = false;
+        p.descs.resize(before);
+        split_emit(p, pc, src_buf, fan_off, nfan, chunk_bytes);
+        return;
     }
     // (see the chunk order in lower)
     if (ld.ss % 4096 == 0 && ls.n * ls.ss < 4096 && nfan <= 2) p.n_spread += p.descs.size() - before;
@@ -1399,12 +1406,16 @@ void lower(Plan &p) {
             // us, to one receiver 59.8 -> 46.2; slower where the rows or
             // parts are not so: 40 heads 87.6 -> 92.8, 64 heads 135 -> 148,
             // and to 4 receivers 94.7 -> 103).
-            std::map<uint32_t, uint64_t> turn;
-            for (auto &k : key) {
-                const uint32_t set = k.first.first;
-                k.first = {uint32_t(turn[set]++), uint64_t(set)};
+            std::vector<std::pair<size_t, size_t>> sets;  // ranges of key, one per set
+            for (size_t i = 0; i < key.size(); ++i) {
+                if (i == 0 || key[i].first.first != key[i - 1].first.first) sets.push_back({i, i});
+                ++sets.back().second;
             }
-            std::stable_sort(key.begin(), key.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+            auto turns = key;
+            for (size_t i = 0; i < key.size();)
+                for (auto &s : sets)
+                    if (s.first < s.second) turns[i++] = key[s.first++];
+            key.swap(turns);
         }
         std::vector<Desc> sorted(p.descs.size());
         for (size_t i = 0; i < key.size(); ++i) sorted[i] = p.descs[key[i].second];
