@@ -113,8 +113,8 @@ typedef struct {
                                LDS per workgroup and rounded down to an even count (a CU's
                                LDS is reserved in two halves); 0 = default, chosen per kernel
                                from its fan-out (32 waves per CU when the plan reads and
-                               writes at most 256 MiB, direct chunks to one receiver
-                               120 MiB; else direct chunks: 16 at fan-out
+                               writes at most 144 MiB, direct chunks to one receiver
+                               120 MiB, unaligned row gathers 256 MiB; else direct chunks: 16 at fan-out
                                <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
                                least 8, except unaligned row gathers with one sender per row,
                                which take 32, 16 and 8 waves at fan-out 1, 2 and above, and

@@ -1399,23 +1399,24 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
     const uint32_t user_lds =
         p.tuning.max_wgs_per_cu ? lds_for_per_half(uint32_t(p.tuning.max_wgs_per_cu) / 2u) : 0u;
     // Those caps are for reshards that stream through HBM.  One whose bytes,
-    // read and written, fit in the last-level cache is bound by latency and
-    // runs with 32 waves per CU (none of its buffers cached before, same
-    // machine, us, capped -> 32 waves: direct fp16 [29,32,10304] to 4
-    // receivers, 96 MB, 26.5 -> 17.8, fp32 [22,192,16,64] to 2, 52 MB, 17.9
-    // -> 13.7; gather fp32 [8,2272,192] to 8, 126 MB, 28.4 -> 22.7; slots
-    // bf16 [10,2157,626] to 4, 135 MB, 42.9 -> 27.0; at 196-279 MB 1.15 to
-    // 1.27 times as fast; past that the caps lead, 52.6 against 59.1 direct
-    // at 315 MB, 215 against 247 slots at 1.1 GB).  Direct chunks to one
-    // receiver, half of whose bytes are reads, turn earlier (fp16
-    // [n,1024,4096] in three layouts, cold, 16 -> 32 waves: 101 MB 20.1 ->
-    // 19.6, 117 MB 23.0 -> 22.4, 134 MB 25.8 -> 26.1, 201 MB 36.5 -> 37.4,
-    // 252 MB 44.7 -> 45.6).
+    // read and written, mostly fit in the last-level cache is bound by
+    // latency and runs with 32 waves per CU.  Where that ends (none of its
+    // buffers cached before, same machine, us, capped -> 32 waves): direct
+    // and row-gather chunks between 144 and 160 MiB (direct fp16 to 4
+    // receivers, 96 MB 26.5 -> 17.8, 126 MB 33.4 -> 23.3, 168 MB 29.7 ->
+    // 31.9, 210 MB 36.6 -> 40.1; to 2, 151 MB 31.4 -> 27.8, 201 MB 34.7 ->
+    // 35.7; gather to 4, 126 MB 29.2 -> 25.0, 168 MB 33.8 -> 34.8), direct
+    // chunks to one receiver, half of whose bytes are reads, between 112 and
+    // 128 MiB (fp16 [n,1024,4096] in three layouts, 117 MB 23.0 -> 22.4, 134
+    // MB 25.8 -> 26.1, 252 MB 44.7 -> 45.6), slots past 256 MiB (bf16
+    // [10,2157,626] to 4, 135 MB, 42.9 -> 27.0; at 196-279 MB 1.15 to 1.27
+    // times as fast; 215 -> 247 at 1.1 GB).
     const int64_t bytes = p.bytes_read + p.bytes_written;
-    const bool cached = bytes <= int64_t(256) << 20;
-    const bool dcached = p.direct_fanout == 1 ? bytes <= int64_t(120) << 20 : cached;
-    const uint32_t cap_lds =
-        p.tuning.cap_is_default ? residency_lds(dcached ? 32u : p.direct_fanout <= 2 ? 16u : 8u, dblock) : user_lds;
+    const bool cached = bytes <= int64_t(144) << 20, cached_slots = bytes <= int64_t(256) << 20;
+    const bool cached_direct = p.direct_fanout == 1 ? bytes <= int64_t(120) << 20 : cached;
+    const uint32_t cap_lds = p.tuning.cap_is_default
+                                 ? residency_lds(cached_direct ? 32u : p.direct_fanout <= 2 ? 16u : 8u, dblock)
+                                 : user_lds;
     const uint32_t n_direct = uint32_t(p.n_direct), n_gather = uint32_t(p.n_gather);
     const uint32_t n_gather_u = uint32_t(p.n_gather_u);
     const uint32_t n_transpose = uint32_t(p.n_transpose);
@@ -1459,7 +1460,7 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         const uint32_t fan = uint32_t(fanout > 0 ? fanout : 1);
         uint32_t waves = 64u / fan > 8u ? 64u / fan : 8u;
         if (segs == 1) waves = fan <= 1 ? 32u : fan == 2 ? 16u : 8u;
-        if ((more_waves || cached) && waves < 32u) waves = 32u;
+        if ((more_waves || cached_slots) && waves < 32u) waves = 32u;
         return residency_lds(waves, block < 256u ? block : 256u);
     };
     if (n_slot) {
