@@ -170,6 +170,7 @@ class Plan:
 
     def __init__(self, handle, shape, src_mesh, dst_mesh, dtype):
         self._h = ctypes.c_void_p(handle)
+        self._destroy = load().reshard_plan_destroy  # the library that made the plan frees it
         self.shape = tuple(shape)
         self.ndim = len(self.shape)
         self.src_mesh = tuple(src_mesh)
@@ -189,8 +190,8 @@ class Plan:
         return self._h
 
     def __del__(self):
-        if getattr(self, "_h", None) and self._h.value and _lib is not None:
-            _lib.reshard_plan_destroy(self._h)
+        if getattr(self, "_destroy", None) and self._h.value:
+            self._destroy(self._h)
             self._h = ctypes.c_void_p(0)
 
 

@@ -219,7 +219,14 @@ int32_t pick_width(uint64_t so, uint64_t dso, int64_t run, const std::vector<Lev
 }
 
 constexpr uint64_t kMaxPieceVectors = (uint64_t(1) << 31) - 1;
-constexpr uint64_t kMaxDescs = uint64_t(1) << 24;  // 1.75 GiB of descriptors
+// (a test builds the planner with smaller limits)
+#ifndef RS_MAX_DESCS
+#define RS_MAX_DESCS (uint64_t(1) << 24)
+#endif
+#ifndef RS_MAX_CHUNK_SPAN
+#define RS_MAX_CHUNK_SPAN (uint64_t(1) << 32)
+#endif
+constexpr uint64_t kMaxDescs = RS_MAX_DESCS;  // 1.75 GiB of descriptors
 
 // Index units per row: vectors on the direct path, whole rows on the
 // realignment path.
@@ -241,7 +248,7 @@ std::pair<uint64_t, uint64_t> piece_off64(const Piece &pc, uint64_t vpr, uint64_
     return {s, t};
 }
 
-constexpr uint64_t kMaxChunkSpan = uint64_t(1) << 32;
+constexpr uint64_t kMaxChunkSpan = RS_MAX_CHUNK_SPAN;
 
 // Byte extents (end of the last byte from the origin) of a piece on the two
 // sides.
@@ -512,7 +519,8 @@ void split_emit(Plan &p, Piece pc, int32_t src_buf, int64_t fan_off, int64_t nfa
 // 154.8 -> 135.4, [4,2000,40,80] 29.1 -> 26.9; to 4 receivers
 // [8,2048,32,128] 110.7 -> 94.7; 1, 2 and 4 KiB blocks within 3 %, 4 KiB
 // ahead on most.  A piece that would be cut into parts of under 4 chunks
-// for it keeps the plain order.
+// for it, at its outer levels or to hold a part within 32-bit offsets, keeps
+// the plain order.
 constexpr int64_t kBlockBytes = 4096;
 
 void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int64_t nfan, int64_t chunk_bytes) {
@@ -528,16 +536,35 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
         return;
     }
     const Level ld = pc.outer.back(), ls = pc.outer[is];
+    const int64_t k = ld.n / T, r = ld.n % T;
+    // Blocks per part: a part lies within 32-bit offsets on both sides, so
+    // split_emit never takes the blocks of one apart (each would be a piece
+    // of its own, kBlockBytes of each of ls.n rows, whatever the chunk size).
+    const uint64_t in_s = uint64_t(T - 1) * uint64_t(ld.ss) + uint64_t(ls.n - 1) * uint64_t(ls.ss) + uint64_t(pc.run);
+    const uint64_t in_d = uint64_t(T - 1) * uint64_t(ld.ds) + uint64_t(ls.n - 1) * uint64_t(ls.ds) + uint64_t(pc.run);
+    int64_t step = 0;
+    if (in_s < kMaxChunkSpan && in_d < kMaxChunkSpan)
+        step = 1 + int64_t(std::min((kMaxChunkSpan - 1 - in_s) / uint64_t(T * ld.ss),
+                                    (kMaxChunkSpan - 1 - in_d) / uint64_t(T * ld.ds)));
+    if (step < k && step * T * ls.n * pc.run < 4 * chunk_bytes) {
+        split_emit(p, pc, src_buf, fan_off, nfan, chunk_bytes);
+        return;
+    }
     Piece sub = pc;
     sub.outer.clear();
     for (size_t i = 0; i + 1 < nl; ++i)
         if (i != is) sub.outer.push_back(pc.outer[i]);
     Piece rest = sub;
-    const int64_t k = ld.n / T, r = ld.n % T;
     sub.outer.push_back({k, ld.ss * T, ld.ds * T});
+    const size_t lk = sub.outer.size() - 1;
     sub.outer.push_back(ls);
     sub.outer.push_back({T, ld.ss, ld.ds});
-    split_emit(p, sub, src_buf, fan_off, nfan, chunk_bytes);
+    for (int64_t k0 = 0; k0 < k && !p.too_many; k0 += step) {
+        sub.outer[lk].n = std::min(step, k - k0);
+        sub.src_off = pc.src_off + uint64_t(k0 * T * ld.ss);
+        sub.dst_off = pc.dst_off + uint64_t(k0 * T * ld.ds);
+        split_emit(p, sub, src_buf, fan_off, nfan, chunk_bytes);
+    }
     if (r && !p.too_many) {
         rest.outer.push_back(ls);
         rest.outer.push_back({r, ld.ss, ld.ds});
@@ -552,6 +579,7 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
         return;
     }
     // (see the chunk order in lower)
+    p.n_blocked += p.descs.size() - before;
     if (ld.ss % 4096 == 0 && ls.n * ls.ss < 4096 && nfan <= 2) p.n_spread += p.descs.size() - before;
 }
 
@@ -1237,7 +1265,9 @@ void lower(Plan &p) {
     p.fan.assign(p.dst.shard_devs.begin(), p.dst.shard_devs.end());
     p.align = 1;
     p.lds_bytes = 0;
+    p.n_blocked = 0;
     p.n_spread = 0;
+    p.sets_in_turn = false;
     p.transpose_lds = 0;
     p.transpose_plain = false;
     p.too_many = false;
@@ -1416,6 +1446,7 @@ void lower(Plan &p) {
                 for (auto &s : sets)
                     if (s.first < s.second) turns[i++] = key[s.first++];
             key.swap(turns);
+            p.sets_in_turn = true;
         }
         std::vector<Desc> sorted(p.descs.size());
         for (size_t i = 0; i < key.size(); ++i) sorted[i] = p.descs[key[i].second];

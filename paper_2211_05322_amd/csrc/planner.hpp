@@ -84,7 +84,9 @@ struct Plan {
     size_t n_unit = 0;         // of them unit-gather chunks, their own kernel);
     size_t n_transpose = 0;    // then n_transpose tile-transpose chunks;
                                // the rest: realignment chunks
+    size_t n_blocked = 0;      // direct chunks in blocks of two dimensions
     size_t n_spread = 0;       // direct chunks whose receiver sets share sender rows (chunk order)
+    bool sets_in_turn = false; // ... and these take turns
     bool transpose_plain = false;  // some transpose tiles write parts of 64-byte groups
     uint32_t transpose_lds = 0;  // LDS bytes of the largest set of tiles moved at once
     std::vector<Seg> segs;     // row-gather segment entries

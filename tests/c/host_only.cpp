@@ -1,0 +1,27 @@
+// The host library (planner, host interpreter) without the HIP part, as a
+// shared object for tests that build the planner with smaller limits or look
+// into a plan.  The entry points that need a GPU answer EUNSUPPORTED.
+#include <cstdint>
+
+#include "reshard.h"
+
+#include "../../paper_2211_05322_amd/csrc/planner.hpp"
+
+namespace rs {
+void release_device_table(const Plan &) {}
+}  // namespace rs
+
+extern "C" {
+reshard_status_t reshard_plan_upload(const reshard_plan_t *) { return RESHARD_EUNSUPPORTED; }
+reshard_status_t reshard_execute(const reshard_plan_t *, void *const *, void *const *, void *) {
+    return RESHARD_EUNSUPPORTED;
+}
+reshard_status_t reshard_execute_noalloc(const reshard_plan_t *, void *const *, void *const *, void *) {
+    return RESHARD_EUNSUPPORTED;
+}
+
+int64_t test_blocked_chunks(const reshard_plan_t *plan) {
+    return int64_t(reinterpret_cast<const rs::Plan *>(plan)->n_blocked);
+}
+int test_sets_in_turn(const reshard_plan_t *plan) { return reinterpret_cast<const rs::Plan *>(plan)->sets_in_turn; }
+}

@@ -1,0 +1,63 @@
+"""Direct pieces taken in blocks of two dimensions: when they are, and that
+tables stay as long as the bytes need.  CPU only."""
+
+import pytest
+
+from paper_2211_05322_amd import binding as B
+from tests import host_only
+from tests.test_permuted_layouts import host_perm_case
+
+
+@pytest.fixture(scope="module")
+def small_span(tmp_path_factory):
+    """Parts of under 256 KiB a side, where the product's lie within 4 GiB."""
+    return host_only.build(tmp_path_factory.mktemp("lib") / "small_span.so", RS_MAX_CHUNK_SPAN=1 << 18)
+
+
+def noalloc_takes(p):
+    """Whether the plan's tables fit reshard_execute_noalloc's scratch (its size check
+    comes before any HIP call; the addresses are never used)."""
+    try:
+        B.reshard_execute_noalloc(p, [4096] * p.n_src, [4096] * p.n_dst, stream=0)
+    except B.ReshardError as e:
+        return e.status != B.RESHARD_EUNSUPPORTED
+    return True
+
+
+# sender pieces of 4 GiB and more on a side: shape, dtype, meshes and specs, permutations, chunk size
+WIDE = [((1, 1 << 20, 64, 128), "bfloat16", (2,), "RS^0RR", (32,), "RRS^0R", None, (0, 2, 1, 3), 0),
+        ((1, 1 << 20, 64, 128), "bfloat16", (2,), "RS^0RR", (32,), "RRS^0R", None, (0, 2, 1, 3), 1 << 20),
+        ((1 << 27, 2, 16), "float32", (1,), "RRR", (1,), "RRR", None, (1, 0, 2), 0),
+        ((13, 1, 34, 11100217), "float64", (1, 2), "S^1S^0RR", (2, 4), "RRRS^0", (3, 0, 2, 1), (0, 1, 3, 2), 1 << 18)]
+
+
+@pytest.mark.parametrize("shape,dt,sm,ss,dm,ds,sp,dp,chunk", WIDE)
+def test_chunks_of_wide_pieces_follow_the_chunk_size(shape, dt, sm, ss, dm, ds, sp, dp, chunk):
+    p = B.reshard_plan(shape, dt, sm, ss, dm, ds, src_perm=sp, dst_perm=dp, chunk_bytes=chunk)
+    st = B.reshard_plan_stats(p)
+    # whole chunks of at least the automatic 16 KiB, and a rest per sender and receiver set
+    assert st["n_descriptors"] <= 1.03 * st["bytes_read"] / max(chunk, 16384) + 4 * p.n_src * p.n_dst
+    if chunk == 1 << 20:
+        assert noalloc_takes(p)
+
+
+# parts of several blocks, a short last part, rows left over, other outer levels;
+# (tensor, the number of parts its largest piece is cut into)
+PARTS = [(((2, 700, 16, 32), "float16", (2,), "RS^0RR", (1, 8), "RRS^1R", (0, 2, 1, 3)), 2),
+         (((1, 640, 16, 64), "float32", (1,), "RRRR", (2, 8), "RRS^1R", (0, 2, 1, 3)), 10),
+         (((1500, 3, 16), "float32", (1,), "RRR", (1,), "RRR", (1, 0, 2)), 2),
+         (((3, 2, 1500, 3, 16), "float32", (1,), "RRRRR", (2,), "RRRRR", (1, 0, 3, 2, 4)), 3)]
+
+
+@pytest.mark.parametrize("case,parts", PARTS)
+@pytest.mark.parametrize("chunk", [0, 512, 3000])
+def test_parts_of_wide_pieces_against_oracle(small_span, case, parts, chunk):
+    shape, dt, sm, ss, dm, ds, dp = case
+    with host_only.using(small_span) as lib:
+        p = host_perm_case(shape, dt, sm, ss, None, dm, ds, dp, chunk_bytes=chunk)
+        assert lib.test_blocked_chunks(p.handle) > 0
+        # one chunk more at most per part, and per sender, receiver set and outer index for the rows left over
+        st = B.reshard_plan_stats(p)
+        c = max(256, (chunk or 4096) // 256 * 256)
+        pieces = st["n_unit_tasks"] * 6
+        assert st["n_descriptors"] <= st["bytes_read"] / c + pieces * (parts + 1)
