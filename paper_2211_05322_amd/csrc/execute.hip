@@ -1647,7 +1647,7 @@ extern "C" reshard_status_t reshard_execute_noalloc(const reshard_plan_t *plan, 
         const size_t dbytes = p->descs.size() * sizeof(Desc);
         const size_t fbytes = p->fan.size() * sizeof(int32_t);
         const size_t soff = (dbytes + fbytes + 15) & ~size_t(15);
-        const size_t total = soff + p->segs.size() * sizeof(Seg);
+        const size_t total = table_bytes(*p);
         if (total > size_t(RESHARD_NOALLOC_MAX_TABLE_BYTES))
             return fail(RESHARD_EUNSUPPORTED, "the plan's tables take " + std::to_string(total) +
                                                   " bytes; reshard_execute_noalloc holds at most " +

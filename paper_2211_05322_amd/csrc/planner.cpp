@@ -5,6 +5,8 @@
 #include <map>
 #include <numeric>
 
+#include "../../include/reshard.h"
+
 namespace rs {
 
 // ---------------------------------------------------------------- parsing
@@ -360,6 +362,12 @@ void emit_realign(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, in
     p.lds_bytes = std::max(p.lds_bytes, realign_lds_bytes(d.batch, m));
 }
 
+// Chunk length in vectors: whole 256-byte groups where the width allows.
+uint64_t chunk_vectors(const Piece &pc, int64_t chunk_bytes) {
+    const uint64_t cv = uint64_t(std::max<int64_t>(1, chunk_bytes / pc.w)), grain = uint64_t(256 / pc.w);
+    return std::max(grain, cv / grain * grain);
+}
+
 // Emit chunks of a piece whose outer list has at most 3 levels and fewer
 // than 2^31 vectors.  Every chunk spans less than 2^32 bytes on both sides.
 void emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int64_t nfan, int64_t chunk_bytes) {
@@ -393,10 +401,7 @@ void emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int64_t nf
     d.src_buf = uint16_t(src_buf);
     d.nfan = uint16_t(nfan);
     d.fan_off = uint32_t(fan_off);
-    // chunk length in vectors: whole 256-byte groups where the width allows
-    uint64_t cv = uint64_t(std::max<int64_t>(1, chunk_bytes / pc.w));
-    const uint64_t grain = uint64_t(256 / pc.w);
-    cv = std::max(grain, cv / grain * grain);
+    const uint64_t cv = chunk_vectors(pc, chunk_bytes);
     if (p.descs.size() + (total + cv - 1) / cv > kMaxDescs) {
         p.too_many = true;
         return;
@@ -508,6 +513,30 @@ void split_emit(Plan &p, Piece pc, int32_t src_buf, int64_t fan_off, int64_t nfa
     }
 }
 
+// Chunks that split_emit cuts a direct piece into (a chunk that spans 2^32
+// bytes, which split_emit halves, counted as one).
+uint64_t split_count(const Piece &pc, int64_t chunk_bytes) {
+    uint64_t rows = 1;
+    for (const auto &l : pc.outer) rows *= uint64_t(l.n);
+    const uint64_t total = units_per_row(pc) * rows;
+    auto peeled = [&] {
+        Piece sub = pc;
+        sub.outer.erase(sub.outer.begin());
+        return uint64_t(pc.outer.front().n) * split_count(sub, chunk_bytes);
+    };
+    if (pc.outer.size() > 3) return peeled();
+    if (!monotone(pc)) {
+        const auto sp = piece_span(pc);
+        if (sp.first >= kMaxChunkSpan || sp.second >= kMaxChunkSpan) return peeled();
+    }
+    const uint64_t cv = chunk_vectors(pc, chunk_bytes);
+    const uint64_t inner = pc.outer.empty() ? 1 : total / uint64_t(pc.outer.front().n);
+    if (total <= kMaxPieceVectors || pc.outer.empty()) return (total + cv - 1) / cv;
+    if (inner > kMaxPieceVectors) return peeled();
+    const uint64_t part = kMaxPieceVectors / inner * inner;
+    return total / part * ((part + cv - 1) / cv) + (total % part + cv - 1) / cv;
+}
+
 // Emit a direct piece.  Short rows that follow one another along one
 // dimension (level d) in the receivers' buffers and along another (level s)
 // in the sender's -- [batch, seq, head, dim] to [batch, head, seq, dim] --
@@ -525,16 +554,16 @@ constexpr int64_t kBlockBytes = 4096;
 
 void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int64_t nfan, int64_t chunk_bytes) {
     const size_t nl = pc.outer.size(), before = p.descs.size();
-    const bool had_too_many = p.too_many;
     size_t is = nl;
     for (size_t i = 0; i + 1 < nl; ++i)
         if (pc.outer[i].ss == pc.run) is = i;
     const int64_t T = kBlockBytes / pc.run;
-    if (pc.realign || pc.w != 16 || is == nl || T < 2 || pc.outer.back().ds != pc.run || pc.outer.back().n <= T ||
+    if (p.shortest_table || pc.realign || pc.w != 16 || is == nl || T < 2 || pc.outer.back().ds != pc.run || pc.outer.back().n <= T ||
         (nl > 2 && pc.outer.back().n * pc.outer[is].n * pc.run < 4 * chunk_bytes)) {
         split_emit(p, pc, src_buf, fan_off, nfan, chunk_bytes);
         return;
     }
+    p.longer_orders = true;
     const Level ld = pc.outer.back(), ls = pc.outer[is];
     const int64_t k = ld.n / T, r = ld.n % T;
     // Blocks per part: a part lies within 32-bit offsets on both sides, so
@@ -572,14 +601,9 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
         rest.dst_off += uint64_t(k * T * ld.ds);
         split_emit(p, rest, src_buf, fan_off, nfan, chunk_bytes);
     }
-    if (p.too_many && !had_too_many) {  // the cuts cost the table its room: plain order
-        p.too_many = false;
-        p.descs.resize(before);
-        split_emit(p, pc, src_buf, fan_off, nfan, chunk_bytes);
-        return;
-    }
-    // (see the chunk order in lower)
+    // (see lower for the chunks that this adds, and for the chunk order)
     p.n_blocked += p.descs.size() - before;
+    p.extra_chunks += int64_t(p.descs.size() - before) - int64_t(split_count(pc, chunk_bytes));
     if (ld.ss % 4096 == 0 && ls.n * ls.ss < 4096 && nfan <= 2) p.n_spread += p.descs.size() - before;
 }
 
@@ -1256,16 +1280,16 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
     return true;
 }
 
-}  // namespace
-
-void lower(Plan &p) {
+void lower_once(Plan &p) {
     const int nd = p.ndim;
     const int64_t es = p.es;
     p.descs.clear();
     p.fan.assign(p.dst.shard_devs.begin(), p.dst.shard_devs.end());
     p.align = 1;
     p.lds_bytes = 0;
+    p.longer_orders = false;
     p.n_blocked = 0;
+    p.extra_chunks = 0;
     p.n_spread = 0;
     p.sets_in_turn = false;
     p.transpose_lds = 0;
@@ -1553,6 +1577,23 @@ void lower(Plan &p) {
         int64_t n = 1;
         for (int64_t x : shp) n *= x;
         p.src_local_numel[dev] = n;
+    }
+}
+
+}  // namespace
+
+// Some orders are faster and take more chunks (extra_chunks) than the plain
+// one.  A plan has them only while its table is within the limits that the
+// plain order would hold it to: the chunk limit, and the scratch of
+// reshard_execute_noalloc.
+void lower(Plan &p) {
+    p.shortest_table = false;
+    lower_once(p);
+    if (!p.longer_orders || p.tile_span_too_long) return;
+    const int64_t limit = RESHARD_NOALLOC_MAX_TABLE_BYTES, bytes = int64_t(table_bytes(p));
+    if (p.too_many || (bytes > limit && bytes - p.extra_chunks * int64_t(sizeof(Desc)) <= limit)) {
+        p.shortest_table = true;
+        lower_once(p);
     }
 }
 

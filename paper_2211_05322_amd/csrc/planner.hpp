@@ -84,6 +84,9 @@ struct Plan {
     size_t n_unit = 0;         // of them unit-gather chunks, their own kernel);
     size_t n_transpose = 0;    // then n_transpose tile-transpose chunks;
                                // the rest: realignment chunks
+    bool shortest_table = false;  // lowered without the orders that take more chunks
+    bool longer_orders = false;   // some piece has such an order,
+    int64_t extra_chunks = 0;     //     and the chunks that these add
     size_t n_blocked = 0;      // direct chunks in blocks of two dimensions
     size_t n_spread = 0;       // direct chunks whose receiver sets share sender rows (chunk order)
     bool sets_in_turn = false; // ... and these take turns
@@ -109,6 +112,13 @@ struct Plan {
     mutable std::mutex mu;
     mutable void *d_table[kMaxHipDevices] = {};
 };
+
+// Bytes of the plan's device tables: descriptors, receiver lists, segment
+// entries (from a 16-byte boundary).
+inline size_t table_bytes(const Plan &p) {
+    const size_t head = p.descs.size() * sizeof(Desc) + p.fan.size() * sizeof(int32_t);
+    return ((head + 15) & ~size_t(15)) + p.segs.size() * sizeof(Seg);
+}
 
 // Returns "" on success, else an error message; `code` receives the status.
 std::string parse_spec(const char *spec, int ndim, int mesh_ndim, std::vector<std::vector<int>> &axes);

@@ -14,6 +14,12 @@ def small_span(tmp_path_factory):
     return host_only.build(tmp_path_factory.mktemp("lib") / "small_span.so", RS_MAX_CHUNK_SPAN=1 << 18)
 
 
+@pytest.fixture(scope="module")
+def few_chunks(tmp_path_factory):
+    """At most 1000 chunks a plan, where the product takes 2^24."""
+    return host_only.build(tmp_path_factory.mktemp("lib") / "few_chunks.so", RS_MAX_DESCS=1000)
+
+
 def noalloc_takes(p):
     """Whether the plan's tables fit reshard_execute_noalloc's scratch (its size check
     comes before any HIP call; the addresses are never used)."""
@@ -61,3 +67,36 @@ def test_parts_of_wide_pieces_against_oracle(small_span, case, parts, chunk):
         c = max(256, (chunk or 4096) // 256 * 256)
         pieces = st["n_unit_tasks"] * 6
         assert st["n_descriptors"] <= st["bytes_read"] / c + pieces * (parts + 1)
+
+
+# many pieces, each a few chunks longer in blocks
+MANY = ("float16", (16,), "RS^0RR", (16,), "RRS^0R")
+
+
+def test_table_within_the_noalloc_scratch_stays_in_it():
+    dt, sm, ss, dm, ds = MANY
+    p = B.reshard_plan((33, 496, 32, 128), dt, sm, ss, dm, ds, dst_perm=(0, 2, 1, 3), chunk_bytes=3968)
+    assert B.reshard_plan_stats(p)["n_descriptors"] == 35072 and noalloc_takes(p)
+    # the plain table would be too long as well: blocks stay
+    q = B.reshard_plan((66, 496, 32, 128), dt, sm, ss, dm, ds, dst_perm=(0, 2, 1, 3), chunk_bytes=3968)
+    assert B.reshard_plan_stats(q)["n_descriptors"] > 2 * 35072 and not noalloc_takes(q)
+
+
+def test_plans_within_the_chunk_limit_stay_in_it(few_chunks):
+    dt, sm, ss, dm, ds = "float16", (4,), "RS^0RR", (4,), "RRS^0R"
+    with host_only.using(few_chunks) as lib:
+        seen = set()
+        for b in range(1, 6):  # 336 b chunks in blocks, 331 b in plain order
+            args = (b, 124, 8, 128), dt, sm, ss
+            try:
+                p = host_perm_case(*args, None, dm, ds, (0, 2, 1, 3), chunk_bytes=1000)
+            except B.ReshardError as e:
+                assert e.status == B.RESHARD_EUNSUPPORTED and b >= 4
+                seen.add("refused")
+                continue
+            assert "refused" not in seen
+            blocked = lib.test_blocked_chunks(p.handle) > 0
+            assert blocked or "blocked" in seen
+            seen.add("blocked" if blocked else "plain")
+            del p
+        assert seen == {"blocked", "plain", "refused"}
