@@ -549,8 +549,14 @@ uint64_t split_count(const Piece &pc, int64_t chunk_bytes) {
 // [8,2048,32,128] 110.7 -> 94.7; 1, 2 and 4 KiB blocks within 3 %, 4 KiB
 // ahead on most.  A piece that would be cut into parts of under 4 chunks
 // for it, at its outer levels or to hold a part within 32-bit offsets, keeps
-// the plain order.
+// the plain order.  So do, as slower in blocks (bf16, 300 MB, plain -> blocks):
+// rows under 128 bytes to more than 4 receivers (8 of them, 16 heads of 32
+// bytes 46.9 -> 58.7 us, of 64 bytes 46.0 -> 48.7; to 4 they gain, 70.0 ->
+// 56.4 and 56.2 -> 51.0), and blocks of 2 or 3 rows of fewer than 4 heads
+// (2 heads of 2 KiB, one receiver 54.6 -> 56.9, 8 receivers 43.2 -> 44.7;
+// 4 heads 55.6 -> 53.5, 4 rows of 2 heads 56.2 -> 52.3).
 constexpr int64_t kBlockBytes = 4096;
+constexpr int64_t kBlockRowMany = 128;  // least row for more than 4 receivers
 
 void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int64_t nfan, int64_t chunk_bytes) {
     const size_t nl = pc.outer.size(), before = p.descs.size();
@@ -558,7 +564,7 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
     for (size_t i = 0; i + 1 < nl; ++i)
         if (pc.outer[i].ss == pc.run) is = i;
     const int64_t T = kBlockBytes / pc.run;
-    if (p.shortest_table || pc.realign || pc.w != 16 || is == nl || T < 2 || pc.outer.back().ds != pc.run || pc.outer.back().n <= T ||
+    if (p.shortest_table || (nfan > 4 && pc.run < kBlockRowMany) || (is < nl && T < 4 && pc.outer[is].n < 4) || pc.realign || pc.w != 16 || is == nl || T < 2 || pc.outer.back().ds != pc.run || pc.outer.back().n <= T ||
         (nl > 2 && pc.outer.back().n * pc.outer[is].n * pc.run < 4 * chunk_bytes)) {
         split_emit(p, pc, src_buf, fan_off, nfan, chunk_bytes);
         return;
@@ -604,7 +610,7 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
     // (see lower for the chunks that this adds, and for the chunk order)
     p.n_blocked += p.descs.size() - before;
     p.extra_chunks += int64_t(p.descs.size() - before) - int64_t(split_count(pc, chunk_bytes));
-    if (ld.ss % 4096 == 0 && ls.n * ls.ss < 4096 && nfan <= 2) p.n_spread += p.descs.size() - before;
+    if (ld.ss % 4096 == 0 && ls.n * ls.ss < 4096 && nfan <= 2 && ls.n * nfan <= 16) p.n_spread += p.descs.size() - before;
 }
 
 #ifndef RS_TMAXW_LOG2
@@ -1459,7 +1465,10 @@ void lower_once(Plan &p) {
             // (2,4) R S^{01} R R -> R R S^1 R, heads outermost: 79.8 -> 68.8
             // us, to one receiver 59.8 -> 46.2; slower where the rows or
             // parts are not so: 40 heads 87.6 -> 92.8, 64 heads 135 -> 148,
-            // and to 4 receivers 94.7 -> 103).
+            // and to 4 receivers 94.7 -> 103; and with more than 16 rows
+            // of all receivers together: 16 heads a set to 2 receivers, 64
+            // bytes each, 70.4 -> 75.6, 128 bytes 71.2 -> 76.3, 32 heads of
+            // 32 bytes to one 59.9 -> 66.3).
             std::vector<std::pair<size_t, size_t>> sets;  // ranges of key, one per set
             for (size_t i = 0; i < key.size(); ++i) {
                 if (i == 0 || key[i].first.first != key[i - 1].first.first) sets.push_back({i, i});

@@ -1,11 +1,12 @@
 """Direct pieces taken in blocks of two dimensions: when they are, and that
-tables stay as long as the bytes need.  CPU only."""
+tables stay as long as the bytes need.  CPU: against the oracle through the
+host interpreter, with a look at the plan.  GPU: the same layouts."""
 
 import pytest
 
 from paper_2211_05322_amd import binding as B
 from tests import host_only
-from tests.test_permuted_layouts import host_perm_case
+from tests.test_permuted_layouts import _gpu_run, host_perm_case
 
 
 @pytest.fixture(scope="module")
@@ -18,6 +19,11 @@ def small_span(tmp_path_factory):
 def few_chunks(tmp_path_factory):
     """At most 1000 chunks a plan, where the product takes 2^24."""
     return host_only.build(tmp_path_factory.mktemp("lib") / "few_chunks.so", RS_MAX_DESCS=1000)
+
+
+@pytest.fixture(scope="module")
+def plain_lib(tmp_path_factory):
+    return host_only.build(tmp_path_factory.mktemp("lib") / "host.so")
 
 
 def noalloc_takes(p):
@@ -100,3 +106,42 @@ def test_plans_within_the_chunk_limit_stay_in_it(few_chunks):
             seen.add("blocked" if blocked else "plain")
             del p
         assert seen == {"blocked", "plain", "refused"}
+
+
+# (tensor, devices on the two sides, the way back, in blocks, receiver sets in turn)
+PATHS = [((2, 40, 16, 32), 2, (8, 2), False, False, False),    # 64-byte rows to 8 receivers
+         ((2, 160, 16, 32), 2, (4, 2), False, True, False),    # to 4
+         ((2, 80, 16, 64), 2, (8, 2), False, True, False),     # 128-byte rows to 8
+         ((2, 16, 8, 1024), 2, (1, 4), False, False, False),   # blocks of 2 rows, 2 heads
+         ((2, 16, 8, 1024), 2, (1, 2), False, True, False),    # 4 heads
+         ((2, 16, 8, 512), 2, (1, 4), False, True, True),      # blocks of 4 rows; rows of heads 8 KiB apart
+         ((2, 160, 64, 32), 2, (1, 4), False, True, True),     # 16 heads a set, one receiver
+         ((2, 160, 64, 32), 2, (2, 4), False, True, False),    # ... two
+         ((2, 160, 64, 32), 2, (2, 8), False, True, True),     # 8 heads a set, two receivers
+         ((2, 130, 32, 64), 2, (2, 5), False, True, True),     # sets of 7 and 6 heads
+         ((2, 128, 32, 64), 2, (2, 5), False, True, True),     # the last block whole
+         ((2, 30, 96, 64), 1, (1, 2), True, True, False),      # the way back: blocks of heads
+         ((2, 33, 130, 32), 2, (1, 3), True, True, False)]     # ... a rest of 1 head, of 65
+
+
+@pytest.mark.parametrize("shape,n,dm,back,blocks,turns", PATHS)
+def test_order_of_head_layouts(plain_lib, shape, n, dm, back, blocks, turns):
+    a, b, perm = "RS^0RR", "RRS^1R", (0, 2, 1, 3)
+    with host_only.using(plain_lib) as lib:
+        if back:
+            p = host_perm_case(shape, "float16", (1, n), b, perm, dm, "RS^1RR", None)
+        else:
+            p = host_perm_case(shape, "float16", (n,), a, None, dm, b, perm)
+        assert (lib.test_blocked_chunks(p.handle) > 0, bool(lib.test_sets_in_turn(p.handle))) == (blocks, turns)
+        del p
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,n,dm,back,blocks,turns", PATHS)
+def test_gpu_order_of_head_layouts(shape, n, dm, back, blocks, turns):
+    print(f"head layout {shape} {n} {dm} back={back}", flush=True)
+    a, b, perm = "RS^0RR", "RRS^1R", (0, 2, 1, 3)
+    if back:
+        _gpu_run(shape, "float16", (1, n), b, perm, dm, "RS^1RR", None)
+    else:
+        _gpu_run(shape, "float16", (n,), a, None, dm, b, perm)
