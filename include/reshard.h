@@ -313,9 +313,8 @@ int64_t reshard_plan_unaligned_gather_chunks(const reshard_plan_t *plan);
 
 /* Of reshard_plan_unaligned_gather_chunks, the number that move 16-byte
  * units of each segment with unaligned loads and stores (one receiver,
- * segments under 2 KiB on average, or two receivers of rows under 8 KiB from
- * one sender; a kernel of their own), or -1 for a NULL
- * plan. */
+ * segments under 2 KiB on average, or two receivers of rows of 128 bytes to
+ * 1 KiB from one sender; a kernel of their own), or -1 for a NULL plan. */
 int64_t reshard_plan_unit_gather_chunks(const reshard_plan_t *plan);
 
 /* Number of workgroup chunks that transpose tiles through LDS (tasks whose

@@ -569,7 +569,7 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
         split_emit(p, pc, src_buf, fan_off, nfan, chunk_bytes);
         return;
     }
-    p.longer_orders = true;
+    p.longer_forms = true;
     const Level ld = pc.outer.back(), ls = pc.outer[is];
     const int64_t k = ld.n / T, r = ld.n % T;
     // Blocks per part: a part lies within 32-bit offsets on both sides, so
@@ -1032,7 +1032,9 @@ void halve_gather_tail(std::vector<Desc> &g, size_t k) {
 #ifndef RS_UNIT_MAX_SEG
 #define RS_UNIT_MAX_SEG 2048  // the unit gather takes mean segment widths below this (bytes)
 #endif
-constexpr int64_t kUnitRow2 = 8192;  // ... and rows below this to two receivers from one sender
+// ... and, to two receivers, rows of one sender from kUnitRow2Least bytes up
+// to below kUnitRow2 (see lower_gather_unaligned)
+constexpr int64_t kUnitRow2Least = 128, kUnitRow2 = 1024;
 
 // Unaligned row gather of one group (see desc.h): segments of any widths
 // tiling the destination row (one segment per row too, when its rows are in
@@ -1191,12 +1193,20 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
     // (or rows), which short segments make frequent.  Measured against
     // destination slots: 8 % faster with 770-byte segments at fan-out 1, 18 %
     // with 4-byte segments among them; slower with rows of 6 KiB and more
-    // from one sender.  Two receivers gain too where a row has one sender, up
-    // to kUnitRow2 bytes (uint8 [64,1025,1001] by 250-byte rows 42.9 -> 38.2
-    // us, 1500-byte rows 262 -> 253, 7000-byte rows 16.2 -> 15.1); with 32
-    // senders per row they lose (228 -> 249), as do 4 receivers and more.
-    const int64_t seg_mean_limit = nfan == 2 && ns == 1 ? kUnitRow2 : int64_t(RS_UNIT_MAX_SEG) * int64_t(ns);
-    bool unit = (nfan <= int64_t(RS_UNIT_MAX_FAN) || (nfan == 2 && ns == 1)) && row_bytes < seg_mean_limit;
+    // from one sender.  Two receivers gain too where a row has one sender and
+    // is short, cold buffers, rows in runs / source rows whole (uint8, 60 MB,
+    // slots -> units): 180 bytes 31.2 -> 27.0 / 16.6 -> 14.5 us, 300 bytes
+    // 29.8 -> 26.0 / 16.7 -> 14.3, 777 bytes 28.5 -> 28.1 / 16.4 -> 15.3;
+    // [64,1025,1001] in 250-byte rows 46.5 -> 44.0, but 34.1 -> 37.3 with its
+    // buffers in the last-level cache.  Longer rows lose (600 MB: 1500 bytes
+    // 112.5 -> 117.3, 5001 bytes 106.7 -> 113.2), and so do shorter ones, whose
+    // rows fill their last unit badly, which the table pays for too (1-byte
+    // rows 165 -> 444, 8 58.3 -> 138.8, 15 60.4 -> 200, 17 58.8 -> 62.9, 63
+    // 58.9 -> 59.5, 130 59.0 -> 56.8).  With 32 senders per row two receivers
+    // lose (228 -> 249), as do 4 receivers and more.
+    bool unit = nfan <= int64_t(RS_UNIT_MAX_FAN) && row_bytes < int64_t(RS_UNIT_MAX_SEG) * int64_t(ns);
+    const bool unit2 = nfan == 2 && ns == 1 && row_bytes >= kUnitRow2Least && row_bytes < kUnitRow2;
+    unit = unit || (unit2 && !p.shortest_table);
     uint32_t upr = 0;  // units per row
     bool unit_short = false;
     for (size_t k = 0; k < ns; ++k) {
@@ -1212,6 +1222,10 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
     if (unit) {
         const uint64_t total = run_rows * upr;
         const uint64_t per = (total + cv - 1) / cv;
+        if (unit2) {
+            p.longer_forms = true;
+            p.extra_chunks += int64_t(per * run_d0.size()) - int64_t(nchunks);
+        }
         if (p.descs.size() + out.size() + unit_out.size() + per * run_d0.size() > kMaxDescs) {
             p.too_many = true;
             return false;
@@ -1293,7 +1307,7 @@ void lower_once(Plan &p) {
     p.fan.assign(p.dst.shard_devs.begin(), p.dst.shard_devs.end());
     p.align = 1;
     p.lds_bytes = 0;
-    p.longer_orders = false;
+    p.longer_forms = false;
     p.n_blocked = 0;
     p.extra_chunks = 0;
     p.n_spread = 0;
@@ -1591,14 +1605,14 @@ void lower_once(Plan &p) {
 
 }  // namespace
 
-// Some orders are faster and take more chunks (extra_chunks) than the plain
-// one.  A plan has them only while its table is within the limits that the
-// plain order would hold it to: the chunk limit, and the scratch of
+// Some forms (blocks of heads, units to two receivers) are faster and take
+// more chunks (extra_chunks) than the general one.  A plan has them only while
+// its table is within the limits that the general form would hold it to: the chunk limit, and the scratch of
 // reshard_execute_noalloc.
 void lower(Plan &p) {
     p.shortest_table = false;
     lower_once(p);
-    if (!p.longer_orders || p.tile_span_too_long) return;
+    if (!p.longer_forms || p.tile_span_too_long) return;
     const int64_t limit = RESHARD_NOALLOC_MAX_TABLE_BYTES, bytes = int64_t(table_bytes(p));
     if (p.too_many || (bytes > limit && bytes - p.extra_chunks * int64_t(sizeof(Desc)) <= limit)) {
         p.shortest_table = true;

@@ -84,8 +84,8 @@ struct Plan {
     size_t n_unit = 0;         // of them unit-gather chunks, their own kernel);
     size_t n_transpose = 0;    // then n_transpose tile-transpose chunks;
                                // the rest: realignment chunks
-    bool shortest_table = false;  // lowered without the orders that take more chunks
-    bool longer_orders = false;   // some piece has such an order,
+    bool shortest_table = false;  // lowered without the forms that take more chunks
+    bool longer_forms = false;    // some group or piece has such a form,
     int64_t extra_chunks = 0;     //     and the chunks that these add
     size_t n_blocked = 0;      // direct chunks in blocks of two dimensions
     size_t n_spread = 0;       // direct chunks whose receiver sets share sender rows (chunk order)

@@ -145,3 +145,16 @@ def test_gpu_order_of_head_layouts(shape, n, dm, back, blocks, turns):
         _gpu_run(shape, "float16", (1, n), b, perm, dm, "RS^1RR", None)
     else:
         _gpu_run(shape, "float16", (n,), a, None, dm, b, perm)
+
+
+def test_units_to_two_receivers_leave_room_in_the_table():
+    # 1-byte rows: slots of 16 of them, never a unit each
+    p = B.reshard_plan((64, 200000, 2), "uint8", (4,), "RS^0R", (2, 2), "RRS^1")
+    st = B.reshard_plan_stats(p)
+    assert B.reshard_plan_unaligned_gather_chunks(p) > 0 and noalloc_takes(p)
+    assert st["n_descriptors"] <= 1.1 * st["bytes_read"] / 4096 + 64 * 8
+    # 129-byte rows, 9 units each: units while their table fits, else slots
+    for rows, units in ((250000, True), (280000, False), (320000, True)):
+        p = B.reshard_plan((2, rows, 258), "uint8", (2,), "RS^0R", (2, 2), "RRS^1", chunk_bytes=4096)
+        assert (B.reshard_plan_unit_gather_chunks(p) > 0) == units, rows
+        assert noalloc_takes(p) == (rows < 300000)

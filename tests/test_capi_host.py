@@ -555,14 +555,17 @@ def test_short_segments_take_units_at_fanout_one(case):
     assert (B.reshard_plan_unit_gather_chunks(p) > 0) == (fanout == 1), fanout
 
 
-# one sender per row to two receivers: rows of 15 to 17 bytes, odd rows, the
-# last row under the unit gather's 8 KiB and the first above it; (case, units)
+# one sender per row to two receivers: the unit gather takes rows from 128
+# bytes to below 1 KiB; (case, units)
 UNIT_PAIR_CASES = [
-    (((4, 70, 30), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), True),     # 15-byte rows: units under 16 bytes
-    (((4, 70, 34), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), True),     # 17-byte rows
+    (((4, 70, 30), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), False),    # 15-byte rows
+    (((4, 70, 34), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), False),    # 17-byte rows
+    (((6, 90, 508), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), False),   # 127-byte rows in runs
+    (((6, 90, 516), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), True),    # 129-byte rows in runs
     (((6, 33, 1001), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), True),   # 251/250-byte rows in runs
-    (((3, 5, 8194), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # 8194-byte rows
-    (((3, 5, 8190), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), True),  # 8190-byte rows
+    (((3, 5, 1022), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), True),   # 1022-byte rows
+    (((3, 5, 1026), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # 1026-byte rows
+    (((3, 5, 8190), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # 8190-byte rows
 ]
 
 
