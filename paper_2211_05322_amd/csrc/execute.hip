@@ -1115,8 +1115,68 @@ __device__ __forceinline__ void tile_store(const Desc &d, const RS_CONST KArgs<N
     }
 }
 
-// R: tile rows a lane loads and exchanges together; G: groups of R vectors
-// per lane loaded before any is written to LDS.
+// Load one tile into its LDS image.  R: tile rows a lane loads and exchanges
+// together; G: groups of R vectors per lane loaded before any is written to
+// LDS.  ra: elements from the tile's first column to the end of the source row.
+template <int ES, uint32_t R, uint32_t G>
+__device__ __forceinline__ void tile_in(const Desc &d, const RS_GLOBAL unsigned char *src, uint32_t at, uint32_t ra,
+                                        uint32_t na, uint32_t nb, uint32_t vl2, unsigned char *lds, uint32_t sp) {
+    constexpr uint32_t V = 16u / ES;
+    const uint32_t nthr = blockDim.x, tid = threadIdx.x, vmask = (1u << vl2) - 1u;
+    const uint32_t nvec = (na + V - 1u) / V, total = (nb + R - 1u) / R << vl2;
+    if (nvec * V <= ra) {
+        // every vector of the tile's rows lies inside its source row:
+        // lanes past the tile repeat its last vectors, so the loads of a
+        // group carry no branches
+        for (uint32_t i0 = tid; i0 < total; i0 += G * nthr) {
+            u32x4 x[G][R];
+#pragma unroll
+            for (uint32_t k = 0; k < G; ++k) {
+                uint32_t i = i0 + k * nthr;
+                i = i < total ? i : total - 1u;
+                uint32_t c = i & vmask;
+                c = c < nvec ? c : nvec - 1u;
+#pragma unroll
+                for (uint32_t q = 0; q < R; ++q) {
+                    uint32_t r = (i >> vl2) * R + q;
+                    r = r < nb ? r : nb - 1u;
+                    x[k][q] = *(const RS_GLOBAL u32x4_u *)(src + (at + r * d.ss[0] + c * 16u));
+                }
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < G; ++k) {
+                const uint32_t i = i0 + k * nthr, c = i & vmask;
+                if (i < total && c < nvec) tile_put<ES, R>(lds, x[k], c * V, (i >> vl2) * R, sp);
+            }
+        }
+    } else {
+        // the tile at the rows' end: the last vector of each is short
+        for (uint32_t i = tid; i < total; i += nthr) {
+            const uint32_t c = i & vmask;
+            if (c >= nvec) continue;
+            u32x4 x[R];
+#pragma unroll
+            for (uint32_t q = 0; q < R; ++q) {
+                uint32_t r = (i >> vl2) * R + q;
+                r = r < nb ? r : nb - 1u;
+                x[q] = tile_load(src + (at + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
+            }
+            tile_put<ES, R>(lds, x, c * V, (i >> vl2) * R, sp);
+        }
+    }
+}
+
+// Store a tile's columns from its LDS image.
+template <int ES, bool PLAIN, int NPTR>
+__device__ __forceinline__ void tile_out(const Desc &d, const RS_CONST KArgs<NPTR> *a, const RS_CONST int32_t *fan,
+                                         const unsigned char *lds, uint32_t sp, uint32_t slots, uint32_t at, uint32_t na,
+                                         uint32_t nb) {
+    for (uint32_t i = threadIdx.x; i < na * slots; i += blockDim.x) {
+        const uint32_t aa = fastdiv(i, d.pad[1], tile_slot_shift(d)), b0 = (i - aa * slots) * (16u / ES);
+        if (b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds, sp, at, nb, aa, b0);
+    }
+}
+
 template <int ES, uint32_t R, uint32_t G, bool PLAIN, int NPTR>
 __device__ __forceinline__ void run_transpose(const Desc &d, const RS_CONST KArgs<NPTR> *a) {
     constexpr uint32_t V = 16u / ES;
@@ -1127,89 +1187,78 @@ __device__ __forceinline__ void run_transpose(const Desc &d, const RS_CONST KArg
     const uint32_t vl2 = tile_row_vecs_log2(d), vmask = (1u << vl2) - 1u;
     const uint32_t step_a = tile_step_a(d), step_b = tile_step_b(d);
     const uint32_t slots = (step_b * ES + 15u) / 16u, sp = tile_slots_padded(slots);
+    const uint32_t rgs = (step_b + R - 1u) / R, each = tile_lds_bytes(step_a, step_b, ES), once = tiles_at_once(each);
+    // the extents of the tile at a position, and the elements to the end of its source rows
+    const auto extents = [&](const TileAt &at, uint32_t &ra, uint32_t &na, uint32_t &nb) {
+        ra = d.run - at.ta * step_a;
+        na = ra < step_a ? ra : step_a;
+        nb = d.batch - at.tb * step_b < step_b ? d.batch - at.tb * step_b : step_b;
+    };
     if (d.v1 - d.v0 == 1u) {
         const TileAt at = tile_offsets(d, d.v0, ES);
-        const uint32_t ra = d.run - at.ta * step_a;  // elements from here to the end of the source row
-        const uint32_t na = ra < step_a ? ra : step_a;
-        const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
-        const uint32_t nvec = (na + V - 1u) / V, total = (nb + R - 1u) / R << vl2;
-        if (nvec * V <= ra) {
-            // every vector of the tile's rows lies inside its source row:
-            // lanes past the tile repeat its last vectors, so the loads of a
-            // group carry no branches
-            for (uint32_t i0 = tid; i0 < total; i0 += G * nthr) {
-                u32x4 x[G][R];
-#pragma unroll
-                for (uint32_t k = 0; k < G; ++k) {
-                    uint32_t i = i0 + k * nthr;
-                    i = i < total ? i : total - 1u;
-                    uint32_t c = i & vmask;
-                    c = c < nvec ? c : nvec - 1u;
-#pragma unroll
-                    for (uint32_t q = 0; q < R; ++q) {
-                        uint32_t r = (i >> vl2) * R + q;
-                        r = r < nb ? r : nb - 1u;
-                        x[k][q] = *(const RS_GLOBAL u32x4_u *)(src + (at.src + r * d.ss[0] + c * 16u));
-                    }
-                }
-#pragma unroll
-                for (uint32_t k = 0; k < G; ++k) {
-                    const uint32_t i = i0 + k * nthr, c = i & vmask;
-                    if (i < total && c < nvec) tile_put<ES, R>(lds, x[k], c * V, (i >> vl2) * R, sp);
-                }
-            }
-        } else {
-            // the tile at the rows' end: the last vector of each is short
-            for (uint32_t i = tid; i < total; i += nthr) {
-                const uint32_t c = i & vmask;
-                if (c >= nvec) continue;
-                u32x4 x[R];
-#pragma unroll
-                for (uint32_t q = 0; q < R; ++q) {
-                    uint32_t r = (i >> vl2) * R + q;
-                    r = r < nb ? r : nb - 1u;
-                    x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
-                }
-                tile_put<ES, R>(lds, x, c * V, (i >> vl2) * R, sp);
-            }
-        }
+        uint32_t ra, na, nb;
+        extents(at, ra, na, nb);
+        tile_in<ES, R, G>(d, src, at.src, ra, na, nb, vl2, lds, sp);
         __syncthreads();
-        for (uint32_t i = tid; i < na * slots; i += nthr) {
-            const uint32_t aa = fastdiv(i, d.pad[1], tile_slot_shift(d)), b0 = (i - aa * slots) * V;
-            if (b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds, sp, at.dst, nb, aa, b0);
-        }
-    } else {
-        // small tiles, as many at once as LDS takes (by default all of the
-        // chunk), each in its own part of it
-        const uint32_t each = tile_lds_bytes(step_a, step_b, ES), rgs = (step_b + R - 1u) / R;
-        const uint32_t once = tiles_at_once(each), per = step_a * slots;
+        tile_out<ES, PLAIN>(d, a, fan, lds, sp, slots, at.dst, na, nb);
+        return;
+    }
+    // Several tiles, as many at once as LDS takes (by default all of the
+    // chunk), each in its own part of it.
+    if (ES == 4 && rgs << vl2 >= nthr) {
+        // Tiles that give every lane a load, one after the other: offsets
+        // once per workgroup, not per lane (fp32 to one receiver, two 8 KiB
+        // tiles a chunk, [2,16384,1824] to [batch, hidden, seq]: 575 vector
+        // instructions per wave by lane, 99.0 -> 88.5 us; [8,2048,3072] 76.7
+        // -> 70.5).  8-byte elements are faster by lane (85 against 96 us),
+        // tiles of 1- and 2-byte ones fill a chunk by themselves.
         for (uint32_t t0 = d.v0, m; t0 < d.v1; t0 += m) {
             m = d.v1 - t0 < once ? d.v1 - t0 : once;
-            for (uint32_t i = tid; i < m * rgs << vl2; i += nthr) {
-                const uint32_t rr = i >> vl2, c = i & vmask, k = rr / rgs, b = (rr - k * rgs) * R;
+            for (uint32_t k = 0; k < m; ++k) {
                 const TileAt at = tile_offsets(d, t0 + k, ES);
-                const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
-                const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
-                if (b >= nb || c * V >= na) continue;
-                u32x4 x[R];
-#pragma unroll
-                for (uint32_t q = 0; q < R; ++q) {
-                    const uint32_t r = b + q < nb ? b + q : nb - 1u;
-                    x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
-                }
-                tile_put<ES, R>(lds + k * each, x, c * V, b, sp);
+                uint32_t ra, na, nb;
+                extents(at, ra, na, nb);
+                tile_in<ES, R, G>(d, src, at.src, ra, na, nb, vl2, lds + k * each, sp);
             }
             __syncthreads();
-            for (uint32_t i = tid; i < m * per; i += nthr) {
-                const uint32_t k = i / per, j = i - k * per;
+            for (uint32_t k = 0; k < m; ++k) {
                 const TileAt at = tile_offsets(d, t0 + k, ES);
-                const uint32_t ra = d.run - at.ta * step_a, na = ra < step_a ? ra : step_a;
-                const uint32_t rb = d.batch - at.tb * step_b, nb = rb < step_b ? rb : step_b;
-                const uint32_t aa = fastdiv(j, d.pad[1], tile_slot_shift(d)), b0 = (j - aa * slots) * V;
-                if (aa < na && b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds + k * each, sp, at.dst, nb, aa, b0);
+                uint32_t ra, na, nb;
+                extents(at, ra, na, nb);
+                tile_out<ES, PLAIN>(d, a, fan, lds + k * each, sp, slots, at.dst, na, nb);
             }
             if (d.v1 - t0 > m) __syncthreads();  // LDS is read before the next tiles are written
         }
+        return;
+    }
+    // the others several to a pass, each lane computing its own tile's offsets
+    const uint32_t per = step_a * slots;
+    for (uint32_t t0 = d.v0, m; t0 < d.v1; t0 += m) {
+        m = d.v1 - t0 < once ? d.v1 - t0 : once;
+        for (uint32_t i = tid; i < m * rgs << vl2; i += nthr) {
+            const uint32_t rr = i >> vl2, c = i & vmask, k = rr / rgs, b = (rr - k * rgs) * R;
+            const TileAt at = tile_offsets(d, t0 + k, ES);
+            uint32_t ra, na, nb;
+            extents(at, ra, na, nb);
+            if (b >= nb || c * V >= na) continue;
+            u32x4 x[R];
+#pragma unroll
+            for (uint32_t q = 0; q < R; ++q) {
+                const uint32_t r = b + q < nb ? b + q : nb - 1u;
+                x[q] = tile_load(src + (at.src + r * d.ss[0] + c * 16u), (ra - c * V) * ES);
+            }
+            tile_put<ES, R>(lds + k * each, x, c * V, b, sp);
+        }
+        __syncthreads();
+        for (uint32_t i = tid; i < m * per; i += nthr) {
+            const uint32_t k = i / per, j = i - k * per;
+            const TileAt at = tile_offsets(d, t0 + k, ES);
+            uint32_t ra, na, nb;
+            extents(at, ra, na, nb);
+            const uint32_t aa = fastdiv(j, d.pad[1], tile_slot_shift(d)), b0 = (j - aa * slots) * V;
+            if (aa < na && b0 < nb) tile_store<ES, PLAIN>(d, a, fan, lds + k * each, sp, at.dst, nb, aa, b0);
+        }
+        if (d.v1 - t0 > m) __syncthreads();  // LDS is read before the next tiles are written
     }
 }
 

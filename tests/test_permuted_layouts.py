@@ -122,7 +122,8 @@ def test_host_transpose_tile_edges(shape, es, fan):
 
 
 # chunks larger than LDS takes at once loop over their tiles
-TILE_LOOPS = [((1, 520, 1040), 2), ((300, 12, 20), 4), ((40, 9, 11), 8), ((1, 1030, 1290), 1)]
+TILE_LOOPS = [((1, 520, 1040), 2), ((300, 12, 20), 4), ((40, 9, 11), 8), ((1, 1030, 1290), 1), ((1, 520, 1040), 4),
+              ((2, 131, 517), 4)]
 
 
 @pytest.mark.parametrize("fan", [1, 4])
@@ -130,6 +131,19 @@ TILE_LOOPS = [((1, 520, 1040), 2), ((300, 12, 20), 4), ((40, 9, 11), 8), ((1, 10
 def test_host_transpose_chunks_of_many_tiles(shape, es, fan):
     p = host_perm_case(shape, _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1), chunk_bytes=1 << 17)
     assert 0 < B.reshard_plan_transpose_chunks(p) <= -(-4 * shape[0] * shape[1] * shape[2] * es // (1 << 17))
+
+
+# several tiles that LDS takes at once: 4-byte elements tile by tile (256 lanes
+# and more of loads each), others and narrow tiles several to a pass
+TILE_SETS = [((1, 520, 1040), 4, 1 << 14), ((2, 131, 517), 4, 1 << 14), ((1, 1040, 1040), 4, 1 << 14),
+             ((3, 260, 33), 4, 1 << 15), ((2, 131, 517), 8, 1 << 14), ((2, 259, 517), 2, 1 << 15)]
+
+
+@pytest.mark.parametrize("fan", [1, 2])
+@pytest.mark.parametrize("shape,es,chunk", TILE_SETS)
+def test_host_transpose_sets_of_tiles(shape, es, chunk, fan):
+    p = host_perm_case(shape, _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1), chunk_bytes=chunk)
+    assert B.reshard_plan_transpose_chunks(p) > 0
 
 
 def test_transpose_table_follows_the_chunk_size():
@@ -287,6 +301,15 @@ def test_gpu_transpose_tile_edges(shape, es, fan):
 def test_gpu_transpose_chunks_of_many_tiles(shape, es, fan):
     print(f"transpose chunks of many tiles {shape} es={es} fan={fan}", flush=True)
     _gpu_run(shape, _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1), chunk_bytes=1 << 17)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fan", [1, 2])
+@pytest.mark.parametrize("shape,es,chunk", TILE_SETS)
+def test_gpu_transpose_sets_of_tiles(shape, es, chunk, fan):
+    print(f"transpose sets of tiles {shape} es={es} chunk={chunk} fan={fan}", flush=True)
+    for kw in ({}, {"block_threads": 64}):
+        _gpu_run(shape, _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1), chunk_bytes=chunk, **kw)
 
 
 @pytest.mark.gpu
