@@ -1033,10 +1033,6 @@ __device__ __forceinline__ void store_low(RS_GLOBAL unsigned char *q, u32x4 y, u
 // against 42 us).  Runs of 32 and 64 were level with 16 on large plans; with
 // few chunks they leave XCDs idle.
 constexpr uint32_t kTGroup = 16;
-// Least LDS per workgroup for plans of 4096 tiles or more: 6 workgroups per
-// CU (measured against uncapped, [8,2047,4098] above 59.7 -> 57.0 us, with 4
-// 56.9, with 2 72.0; fp16 [5,176,48,5376] at fan-out 2 263 -> 260, 281, 396).
-constexpr uint32_t kTLeastLds = 27000;
 
 // tile_put: the vectors x of rows b .. b + R - 1 (b a multiple of R), tile
 // columns a0 .. a0 + 16 / ES - 1, to the LDS image.
@@ -1531,10 +1527,9 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         if (st != RESHARD_OK) return st;
     }
     if (n_transpose) {
-        // the largest tile of the plan in LDS; no residency cap
         a.descs = descs + n_direct + n_gather + n_gather_u;
         const uint32_t tblock = block < 256u ? block : 256u;
-        const uint32_t lds = std::max<uint32_t>(p.transpose_lds, n_transpose >= 4096u ? kTLeastLds : 0u);
+        const uint32_t lds = transpose_launch_lds(p, user_lds);
         a.group = p.transpose_plain ? std::max(1u, std::min<uint32_t>(kTGroup, n_transpose / 64u)) : 1u;
         const auto go = [&](auto es, auto fan, auto plain) {
             return launch_one(reshard_transpose_kernel<NPTR, decltype(es)::value, decltype(fan)::value, decltype(plain)::value>,

@@ -120,6 +120,23 @@ inline size_t table_bytes(const Plan &p) {
     return ((head + 15) & ~size_t(15)) + p.segs.size() * sizeof(Seg);
 }
 
+// LDS per workgroup of the tile transpose's launch: its largest set of tiles,
+// and at least what the cap on resident workgroups reserves (user_lds: the
+// caller's; by default 6 per CU for 4096 chunks and more).  Measured against
+// no cap: bf16 [8,2047,4098] to [batch, hidden, seq] 59.7 -> 57.0 us (4 per CU
+// 56.9, 2 72.0), fp16 [5,176,48,5376] at fan-out 2 263 -> 260 (281, 396),
+// uint8 [16,17408,344] to 4 receivers 103.4 -> 94.9.  4- and 8-byte elements
+// to one or two receivers lose and have none (fp32 [16,4400,864] 117.3 against
+// 122.6, int64 [2,8192,1824] 84.9 against 92.8, fp32 [16,4352,576] to two
+// 103.3 against 107.1); at more the two are level or the cap is ahead (int64
+// [16,2200,192] to 8 143.3 -> 133.8).
+constexpr uint32_t kTLeastLds = 27000;
+inline uint32_t transpose_launch_lds(const Plan &p, uint32_t user_lds) {
+    uint32_t least = user_lds;
+    if (p.tuning.cap_is_default) least = p.n_transpose >= 4096 && (p.es <= 2 || p.max_fanout > 2) ? kTLeastLds : 0u;
+    return p.transpose_lds > least ? p.transpose_lds : least;
+}
+
 // Returns "" on success, else an error message; `code` receives the status.
 std::string parse_spec(const char *spec, int ndim, int mesh_ndim, std::vector<std::vector<int>> &axes);
 std::string build_layout(const std::vector<int64_t> &shape, const std::vector<int64_t> &mesh,

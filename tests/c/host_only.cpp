@@ -23,5 +23,8 @@ reshard_status_t reshard_execute_noalloc(const reshard_plan_t *, void *const *, 
 int64_t test_blocked_chunks(const reshard_plan_t *plan) {
     return int64_t(reinterpret_cast<const rs::Plan *>(plan)->n_blocked);
 }
+uint32_t test_transpose_launch_lds(const reshard_plan_t *plan, uint32_t user_lds) {
+    return rs::transpose_launch_lds(*reinterpret_cast<const rs::Plan *>(plan), user_lds);
+}
 int test_sets_in_turn(const reshard_plan_t *plan) { return reinterpret_cast<const rs::Plan *>(plan)->sets_in_turn; }
 }

@@ -2,8 +2,10 @@
 
 import contextlib
 import ctypes
+import functools
 import os
 import subprocess
+import tempfile
 
 from paper_2211_05322_amd import binding as B
 
@@ -21,8 +23,15 @@ def build(out, **limits):
     assert r.returncode == 0, r.stderr[-4000:]
     lib = B.load(str(out))
     lib.test_blocked_chunks.argtypes = lib.test_sets_in_turn.argtypes = [ctypes.c_void_p]
+    lib.test_transpose_launch_lds.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
     lib.test_blocked_chunks.restype = ctypes.c_int64
     return lib
+
+
+@functools.lru_cache(maxsize=None)
+def plain():
+    """The product's host code and limits."""
+    return build(os.path.join(tempfile.mkdtemp(prefix="reshard_host_"), "host.so"))
 
 
 @contextlib.contextmanager

@@ -21,11 +21,6 @@ def few_chunks(tmp_path_factory):
     return host_only.build(tmp_path_factory.mktemp("lib") / "few_chunks.so", RS_MAX_DESCS=1000)
 
 
-@pytest.fixture(scope="module")
-def plain_lib(tmp_path_factory):
-    return host_only.build(tmp_path_factory.mktemp("lib") / "host.so")
-
-
 def noalloc_takes(p):
     """Whether the plan's tables fit reshard_execute_noalloc's scratch (its size check
     comes before any HIP call; the addresses are never used)."""
@@ -125,9 +120,9 @@ PATHS = [((2, 40, 16, 32), 2, (8, 2), False, False, False),    # 64-byte rows to
 
 
 @pytest.mark.parametrize("shape,n,dm,back,blocks,turns", PATHS)
-def test_order_of_head_layouts(plain_lib, shape, n, dm, back, blocks, turns):
+def test_order_of_head_layouts(shape, n, dm, back, blocks, turns):
     a, b, perm = "RS^0RR", "RRS^1R", (0, 2, 1, 3)
-    with host_only.using(plain_lib) as lib:
+    with host_only.using(host_only.plain()) as lib:
         if back:
             p = host_perm_case(shape, "float16", (1, n), b, perm, dm, "RS^1RR", None)
         else:

@@ -18,6 +18,7 @@ import pytest
 
 import oracle
 from paper_2211_05322_amd import binding as B
+from tests import host_only
 from tests.test_capi_host import run_host
 from tests.test_oracle_pins import fmt_spec, random_dims
 
@@ -172,6 +173,23 @@ def heads_case(run, shape, dt, sm, dm, back):
 def test_host_heads(shape, dt, sm, dm, back):
     p = heads_case(host_perm_case, shape, dt, sm, dm, back)
     assert B.reshard_plan_transpose_chunks(p) == 0
+
+
+# (bytes per element, receivers, the caller's cap, LDS reserved where the caller's cap is 20000 bytes)
+@pytest.mark.parametrize("es,fan,cap,least", [(1, 1, 0, 27000), (2, 2, 0, 27000), (4, 1, 0, 0), (4, 2, 0, 0), (8, 2, 0, 0),
+                                              (4, 3, 0, 27000), (8, 8, 0, 27000),
+                                              (2, 1, -1, 0), (8, 8, -1, 0), (2, 1, 8, 20000)])
+def test_transposes_keep_the_callers_cap(es, fan, cap, least):
+    def lds(shape, cap):
+        p = B.reshard_plan(shape, _TILE_DT[es], (1,), "RRR", (fan,), "RRR", dst_perm=(0, 2, 1), max_wgs_per_cu=cap)
+        many = B.reshard_plan_transpose_chunks(p) >= 4096
+        return many, lib.test_transpose_launch_lds(p.handle, 20000 if cap > 0 else 0)
+
+    with host_only.using(host_only.plain()) as lib:
+        for shape in ((1, 64, 64), (8, 4096, 4096)):
+            many, own = lds(shape, -1)  # no cap: what the tiles take
+            assert many == (shape[0] == 8) and 0 < own <= 32768
+            assert lds(shape, cap)[1] == max(own, least if many or cap > 0 else 0)
 
 
 def test_permuted_outer_dims_need_no_transpose():
