@@ -1024,14 +1024,14 @@ __device__ __forceinline__ void store_low(RS_GLOBAL unsigned char *q, u32x4 y, u
 //
 // What is left is HBM's: columns that do not start on 64-byte boundaries
 // write the two ends of each column of each tile as parts of what memory
-// writes at once.  PLAIN kernels (the plan has such tiles) store them through
+// writes at once.  PLAIN kernels (enough of the plan's tiles do) store through
 // L2, and take kTGroup consecutive chunks on one XCD, so that a neighbouring
 // tile's part meets them there (fp16 [23,1008,8640] (4,8) R S^1 R -> R R
-// S^{01}: non-temporal stores, chunks in turn 335 us; plain stores 256; runs
-// of 8 chunks 235; both 198).  Other tiles keep non-temporal stores, which
-// beat plain ones there (int64 650 x 4480 transposed to 8 receivers 35
-// against 42 us).  Runs of 32 and 64 were level with 16 on large plans; with
-// few chunks they leave XCDs idle.
+// S^{01}, cold buffers, non-temporal / plain stores: chunks in turn 280 / 257
+// us, runs of 8 214 / 199, runs of 16 213 / 194; the kernel before 516).
+// Other plans keep non-temporal stores, which beat plain ones there (int64
+// 650 x 4480 transposed to 8 receivers 35 against 42 us).  Runs of 32 and 64
+// were level with 16 on large plans; with few chunks they leave XCDs idle.
 constexpr uint32_t kTGroup = 16;
 
 // tile_put: the vectors x of rows b .. b + R - 1 (b a multiple of R), tile

@@ -765,11 +765,13 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
     // groups: 204 and 159).  Where columns follow one another in the buffer,
     // a tile's bytes are one run, with two parts in all: not counted from
     // 2 KiB on (fp16 [12,48,11008] to 4 receivers, 96-byte columns: 11.2 us
-    // non-temporal, 13.3 plain).
+    // non-temporal, 13.3 plain).  One kernel takes the plan's tiles one way
+    // (see lower_once).
     const bool dense = tr == tp.nb && tp.ds_a == tp.nb * es && ta * tp.nb * es >= 2048;
-    p.transpose_plain = p.transpose_plain ||
-                        (!dense && (tp.dst_off % kTilePart || tp.ds_a % kTilePart || o1.ds % kTilePart || o2.ds % kTilePart ||
-                                    tr * es % kTilePart));
+    p.n_tiles += tiles;
+    if (!dense && (tp.dst_off % kTilePart || tp.ds_a % kTilePart || o1.ds % kTilePart || o2.ds % kTilePart ||
+                   tr * es % kTilePart))
+        p.n_part_tiles += tiles;
     const FastDiv fsl = make_fastdiv(uint32_t((tr * es + 15) / 16));
     d.pad[0] = vl2 | (fsl.shift << 8);
     d.pad[1] = fsl.mul;
@@ -1313,6 +1315,7 @@ void lower_once(Plan &p) {
     p.n_spread = 0;
     p.sets_in_turn = false;
     p.transpose_lds = 0;
+    p.n_tiles = p.n_part_tiles = 0;
     p.transpose_plain = false;
     p.too_many = false;
     p.tile_span_too_long = false;
@@ -1530,6 +1533,15 @@ void lower_once(Plan &p) {
     p.descs.insert(p.descs.begin() + std::ptrdiff_t(p.n_direct + p.n_gather + p.n_gather_u), tdescs.begin(),
                    tdescs.end());
     p.n_transpose = tdescs.size();
+    // Plain stores, and runs of chunks on one XCD, where more than one tile in
+    // seven writes parts of 64-byte groups, of 8-byte elements two in nine
+    // (a destination split in n, one part of it off: plain against all
+    // non-temporal, in turn, 480 MB to 1, 2, 4 and 8 receivers: fp16 1/5 99,
+    // 106, 125, 115 against 112, 112, 133, 117 us, 1/8 111, 114, 120, 101
+    // against 112, 113, 121, 99; int64 1/4 115, 109, 116, 116 against 116,
+    // 112, 125, 119, 1/8 118, 112, 115, 106 against 116, 108, 112, 95;
+    // storing each piece its own way within the runs measured as all plain).
+    p.transpose_plain = es == 8 ? 9 * p.n_part_tiles > 2 * p.n_tiles : 7 * p.n_part_tiles > p.n_tiles;
     if (p.descs.size() > kMaxDescs) p.too_many = true;
     p.n_phase1 = p.n_direct;
     if (p.flags & 0x20u) {

@@ -90,7 +90,8 @@ struct Plan {
     size_t n_blocked = 0;      // direct chunks in blocks of two dimensions
     size_t n_spread = 0;       // direct chunks whose receiver sets share sender rows (chunk order)
     bool sets_in_turn = false; // ... and these take turns
-    bool transpose_plain = false;  // some transpose tiles write parts of 64-byte groups
+    uint64_t n_tiles = 0, n_part_tiles = 0;  // transpose tiles; those that write parts of 64-byte groups
+    bool transpose_plain = false;  // stored through L2 (enough of these)
     uint32_t transpose_lds = 0;  // LDS bytes of the largest set of tiles moved at once
     std::vector<Seg> segs;     // row-gather segment entries
     int64_t gather_fanout = 0; // largest receiver count among row-gather chunks

@@ -26,5 +26,8 @@ int64_t test_blocked_chunks(const reshard_plan_t *plan) {
 uint32_t test_transpose_launch_lds(const reshard_plan_t *plan, uint32_t user_lds) {
     return rs::transpose_launch_lds(*reinterpret_cast<const rs::Plan *>(plan), user_lds);
 }
+int test_transpose_plain(const reshard_plan_t *plan) {
+    return reinterpret_cast<const rs::Plan *>(plan)->transpose_plain;
+}
 int test_sets_in_turn(const reshard_plan_t *plan) { return reinterpret_cast<const rs::Plan *>(plan)->sets_in_turn; }
 }

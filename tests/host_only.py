@@ -23,6 +23,7 @@ def build(out, **limits):
     assert r.returncode == 0, r.stderr[-4000:]
     lib = B.load(str(out))
     lib.test_blocked_chunks.argtypes = lib.test_sets_in_turn.argtypes = [ctypes.c_void_p]
+    lib.test_transpose_plain.argtypes = [ctypes.c_void_p]
     lib.test_transpose_launch_lds.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
     lib.test_blocked_chunks.restype = ctypes.c_int64
     return lib

@@ -192,6 +192,18 @@ def test_transposes_keep_the_callers_cap(es, fan, cap, least):
             assert lds(shape, cap)[1] == max(own, least if many or cap > 0 else 0)
 
 
+# one of n destination parts has columns off 64-byte groups: stored through
+# L2 when that is more than 1/7 of the tiles, 2/9 for 8-byte elements
+@pytest.mark.parametrize("es,n,off,plain", [(2, 4, 0, False), (2, 8, 1, False), (1, 8, 1, False), (2, 5, 1, True),
+                                            (4, 8, 1, False), (4, 5, 1, True), (8, 8, 1, False), (8, 5, 1, False),
+                                            (8, 4, 1, True), (2, 8, 7, True), (2, 1, 1, True)])
+def test_transpose_stores_by_the_share_of_parts(es, n, off, plain):
+    with host_only.using(host_only.plain()) as lib:
+        p = host_perm_case((1, n * (1088 // es) + off, 80), _TILE_DT[es], (1,), "RRR", None, (2, n), "RS^1R", (0, 2, 1))
+        assert bool(lib.test_transpose_plain(p.handle)) == plain
+        del p
+
+
 def test_permuted_outer_dims_need_no_transpose():
     # same innermost dimension on both sides, outer dimensions swapped: the
     # direct path with per-side strides, no tile transposes
