@@ -113,9 +113,12 @@ typedef struct {
                                LDS per workgroup and rounded down to an even count (a CU's
                                LDS is reserved in two halves); 0 = default, chosen per kernel
                                from its fan-out (32 waves per CU when the plan reads and
-                               writes at most 144 MiB, direct chunks to one receiver
-                               120 MiB, unaligned row gathers 256 MiB; else direct chunks: 16 at fan-out
-                               <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
+                               writes at most 144 MiB, direct chunks to one receiver 120
+                               and to more than 8 64 MiB, unaligned row gathers 256 MiB, to
+                               more than 8 receivers 96, and slots with one sender per row
+                               192 at fan-out 5 and 6, 40 above, of parts of the sender's
+                               rows 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and
+                               above; else direct chunks: 16 at fan-out <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
                                least 8, except unaligned row gathers with one sender per row,
                                which take 32, 16 and 8 waves at fan-out 1, 2 and above, and
                                32 at any fan-out when their chunks are under 3/4 full on

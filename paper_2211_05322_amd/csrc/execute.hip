@@ -1453,12 +1453,12 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
     // 35.7; gather to 4, 126 MB 29.2 -> 25.0, 168 MB 33.8 -> 34.8), direct
     // chunks to one receiver, half of whose bytes are reads, between 112 and
     // 128 MiB (fp16 [n,1024,4096] in three layouts, 117 MB 23.0 -> 22.4, 134
-    // MB 25.8 -> 26.1, 252 MB 44.7 -> 45.6), slots past 256 MiB (bf16
-    // [10,2157,626] to 4, 135 MB, 42.9 -> 27.0; at 196-279 MB 1.15 to 1.27
-    // times as fast; 215 -> 247 at 1.1 GB).
+    // MB 25.8 -> 26.1, 252 MB 44.7 -> 45.6).  Slots and direct chunks to
+    // more than 8 receivers: cached_slots_limit, cached_direct_limit (units
+    // 256 MiB).
     const int64_t bytes = p.bytes_read + p.bytes_written;
-    const bool cached = bytes <= int64_t(144) << 20, cached_slots = bytes <= int64_t(256) << 20;
-    const bool cached_direct = p.direct_fanout == 1 ? bytes <= int64_t(120) << 20 : cached;
+    const bool cached = bytes <= int64_t(144) << 20;
+    const bool cached_direct = bytes <= cached_direct_limit(p.direct_fanout);
     const uint32_t cap_lds = p.tuning.cap_is_default
                                  ? residency_lds(cached_direct ? 32u : p.direct_fanout <= 2 ? 16u : 8u, dblock)
                                  : user_lds;
@@ -1500,18 +1500,20 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
     // its latency is not hidden, and 32 waves are best (8 KiB runs at
     // fan-out 4: 141 against 197 us).  Segments under 16 bytes (the slow
     // slot path) want 32 waves too (fan-out 4: 382 against 390 us).
-    auto gather_u_lds = [&](int64_t fanout, int64_t segs, bool more_waves) {
+    auto gather_u_lds = [&](int64_t fanout, int64_t segs, int64_t cached_limit, bool more_waves) {
         if (!p.tuning.cap_is_default) return user_lds;
         const uint32_t fan = uint32_t(fanout > 0 ? fanout : 1);
         uint32_t waves = 64u / fan > 8u ? 64u / fan : 8u;
         if (segs == 1) waves = fan <= 1 ? 32u : fan == 2 ? 16u : 8u;
-        if ((more_waves || cached_slots) && waves < 32u) waves = 32u;
+        if ((more_waves || bytes <= cached_limit) && waves < 32u) waves = 32u;
         return residency_lds(waves, block < 256u ? block : 256u);
     };
     if (n_slot) {
         const bool short_chunks = p.gather_u_segs == 1 && 4 * p.gather_u_bytes < 3 * p.gather_u_room;
         const bool short_segs = p.gather_u_short && p.gather_u_fanout <= 4;  // measured up to fan-out 4
-        const uint32_t ulds = gather_u_lds(p.gather_u_fanout, p.gather_u_segs, short_chunks || short_segs);
+        const uint32_t ulds = gather_u_lds(p.gather_u_fanout, p.gather_u_segs,
+                                           cached_slots_limit(p.gather_u_fanout, p.gather_u_segs, p.gather_u_parts),
+                                           short_chunks || short_segs);
         a.descs = descs + n_direct + n_gather;
         const reshard_status_t st = launch_one(reshard_gather_u_kernel<NPTR>, a, n_slot, remap,
                                                block < 256u ? block : 256u,
@@ -1519,7 +1521,7 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         if (st != RESHARD_OK) return st;
     }
     if (n_unit) {
-        const uint32_t ulds = gather_u_lds(p.unit_fanout, p.unit_segs, false);
+        const uint32_t ulds = gather_u_lds(p.unit_fanout, p.unit_segs, int64_t(256) << 20, false);
         a.descs = descs + n_direct + n_gather + n_slot;
         const reshard_status_t st = launch_one(reshard_gather_unit_kernel<NPTR>, a, n_unit, remap,
                                                block < 256u ? block : 256u, ulds > kUnitLds ? ulds : kUnitLds,

@@ -1298,6 +1298,7 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
         p.gather_u_fanout = std::max(p.gather_u_fanout, nfan);
         p.gather_u_segs = std::max(p.gather_u_segs, int64_t(ns));
         p.gather_u_short = p.gather_u_short || (d.ds[0] & kUShortSegs) != 0;
+        p.gather_u_parts = p.gather_u_parts || (ns == 1 && !lv.empty() && lv[0].ss[0] != row_bytes);
     }
     return true;
 }
@@ -1333,6 +1334,7 @@ void lower_once(Plan &p) {
     p.gather_u_bytes = 0;
     p.gather_u_room = 0;
     p.gather_u_short = false;
+    p.gather_u_parts = false;
     p.unit_fanout = 0;
     p.unit_segs = 0;
     std::vector<Desc> gdescs, udescs, unitdescs;

@@ -97,6 +97,7 @@ struct Plan {
     int64_t gather_fanout = 0; // largest receiver count among row-gather chunks
     int64_t gather_u_fanout = 0; // ... among unaligned row-gather chunks
     int64_t gather_u_segs = 0;   // most segments per row among unaligned row-gather groups
+    bool gather_u_parts = false; // some one-sender slot group reads parts of its sender's rows
     uint64_t gather_u_bytes = 0; // destination bytes of the slot chunks, and their nominal
     uint64_t gather_u_room = 0;  //     capacity (chunks x chunk size): how full they are
     bool gather_u_short = false; // some slot group has segments under 16 bytes
@@ -119,6 +120,32 @@ struct Plan {
 inline size_t table_bytes(const Plan &p) {
     const size_t head = p.descs.size() * sizeof(Desc) + p.fan.size() * sizeof(int32_t);
     return ((head + 15) & ~size_t(15)) + p.segs.size() * sizeof(Seg);
+}
+
+// Bytes read and written up to which a reshard runs with 32 waves per CU
+// instead of its kernel's cap (why: launch).  Direct chunks, by receivers:
+// to 16 cold buffers 50 MB 1.04 times as fast, 90 MB 0.97, 130 MB 0.95.
+inline int64_t cached_direct_limit(int64_t fanout) {
+    return int64_t(fanout == 1 ? 120 : fanout > 8 ? 64 : 144) << 20;
+}
+// Slots, by receivers, senders per row, and whether a sender's rows follow one
+// another.  Rows from one sender fill the cap's fewer waves well, and the more
+// receivers, the sooner they lose with 32 waves, parts of wider rows first
+// (times as fast, buffers cold / warm): to 2, parts 200 MB 1.02 / 0.98, 230 MB
+// 0.97 / 0.95, whole rows 1.0; to 3, 262 MB 1.2 to 1.4 / 1.05 to 1.2; to 4,
+// parts 165 MB 1.5 / 1.25, 171 MB 1.05 / 0.88, whole rows 262 MB 0.95 to
+// 1.14 / 0.92 to 1.12; to 5, whole rows 200 MB 1.11 / 1.06, 230 MB 0.93 / 0.92;
+// to 6, whole rows 180 MB 0.94 and 1.19 / 0.93 and 1.17, 262 MB 0.92, parts
+// 25 MB 1.06, 90 MB 1.05 / 0.88; to 7, 90 MB 0.93; to 8, 40 MB 1.05, 70 MB 0.92
+// to 0.95, 262 MB 0.83 to 0.89.  From several senders: to 4 and 8, 1.02 to
+// 1.1 up to 262 MB (bf16 [10,2157,626] to 4, 135 MB, 42.9 -> 27.0 us; 215 ->
+// 247 at 1.1 GB); to 16, 90 MB 1.02 / 0.99, 130 MB 0.96.
+inline int64_t cached_slots_limit(int64_t fanout, int64_t senders, bool parts) {
+    int64_t mib = 256;
+    if (senders > 1) mib = fanout > 8 ? 96 : 256;
+    else if (parts) mib = fanout <= 2 ? 200 : fanout == 3 ? 256 : fanout <= 5 ? 160 : 40;
+    else if (fanout > 4) mib = fanout <= 6 ? 192 : 40;
+    return mib << 20;
 }
 
 // LDS per workgroup of the tile transpose's launch: its largest set of tiles,

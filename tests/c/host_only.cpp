@@ -29,5 +29,11 @@ uint32_t test_transpose_launch_lds(const reshard_plan_t *plan, uint32_t user_lds
 int test_transpose_plain(const reshard_plan_t *plan) {
     return reinterpret_cast<const rs::Plan *>(plan)->transpose_plain;
 }
+int64_t test_cached_limit(int64_t fanout, int64_t senders, int parts) {  // no senders: direct chunks
+    return senders > 0 ? rs::cached_slots_limit(fanout, senders, parts != 0) : rs::cached_direct_limit(fanout);
+}
+int test_slots_of_parts(const reshard_plan_t *plan) {
+    return reinterpret_cast<const rs::Plan *>(plan)->gather_u_parts;
+}
 int test_sets_in_turn(const reshard_plan_t *plan) { return reinterpret_cast<const rs::Plan *>(plan)->sets_in_turn; }
 }

@@ -23,9 +23,11 @@ def build(out, **limits):
     assert r.returncode == 0, r.stderr[-4000:]
     lib = B.load(str(out))
     lib.test_blocked_chunks.argtypes = lib.test_sets_in_turn.argtypes = [ctypes.c_void_p]
+    lib.test_cached_limit.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    lib.test_slots_of_parts.argtypes = [ctypes.c_void_p]
     lib.test_transpose_plain.argtypes = [ctypes.c_void_p]
     lib.test_transpose_launch_lds.argtypes = [ctypes.c_void_p, ctypes.c_uint32]
-    lib.test_blocked_chunks.restype = ctypes.c_int64
+    lib.test_blocked_chunks.restype = lib.test_cached_limit.restype = ctypes.c_int64
     return lib
 
 

@@ -18,6 +18,7 @@ import pytest
 import oracle
 from paper_2211_05322_amd import binding as B
 from paper_2211_05322_amd.workloads import WORKLOADS
+from tests import host_only
 from tests.test_oracle_pins import fmt_spec, random_dims
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -576,6 +577,31 @@ def test_host_units_to_two_receivers(case, units, chunk):
     assert B.reshard_plan_unaligned_gather_chunks(p) > 0
     assert (B.reshard_plan_unit_gather_chunks(p) > 0) == units
     host_case(*case, chunk_bytes=chunk)
+
+
+def test_waves_of_cached_reshards_as_the_header_says():
+    """The sizes up to which 32 waves per CU are the default are those the header names."""
+    lib = host_only.plain()
+
+    def mib(senders, parts, *fanouts):
+        return [lib.test_cached_limit(f, senders, parts) >> 20 for f in fanouts]
+    assert mib(0, 0, 1, 2, 8, 9, 32) == [120, 144, 144, 64, 64]
+    assert mib(2, 0, 1, 2, 8, 9, 32) == mib(2, 1, 1, 2, 8, 9, 32) == [256, 256, 256, 96, 96]
+    assert mib(1, 0, 1, 2, 4, 5, 6, 7, 32) == [256, 256, 256, 192, 192, 40, 40]
+    assert mib(1, 1, 1, 2, 3, 4, 5, 6, 32) == [200, 200, 256, 160, 160, 40, 40]
+    text = " ".join(open(HEADER).read().split())
+    for words in ("at most 144 MiB, direct chunks to one receiver 120 and to more than 8 64 MiB",
+                  "unaligned row gathers 256 MiB, to more than 8 receivers 96",
+                  "slots with one sender per row 192 at fan-out 5 and 6, 40 above",
+                  "of parts of the sender's rows 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and above"):
+        assert words in text
+    with host_only.using(lib):
+        for case, parts in ((((9, 160, 1233), "bfloat16", (4,), "S^0RR", (4, 2), "S^1RR"), False),
+                            (((57, 66, 3697), "bfloat16", (2, 4), "RS^0R", (2, 4), "RRS^0"), True)):
+            p = plan_of(*case)
+            assert B.reshard_plan_unaligned_gather_chunks(p) > 0
+            assert bool(lib.test_slots_of_parts(p.handle)) == parts
+            del p
 
 
 def test_gather_used_by_column_split_workloads():
