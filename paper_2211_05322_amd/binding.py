@@ -226,8 +226,12 @@ def _stream_handle(stream):
         import torch
         if torch.cuda.is_initialized():
             # the handle alone: torch.cuda.current_stream() builds a Stream
-            # object around it, 2.7 us of a call's 7 (0.2 us this way)
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            # object around it, 2.7 us of a call's 7 (0.2 us this way); a
+            # torch without these private functions takes that way
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream

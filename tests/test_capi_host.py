@@ -34,6 +34,20 @@ def declared_functions():
     return sorted(set(re.findall(r"\b(reshard_[a-z_]+)\s*\(", text)))
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_handle_without_torchs_private_functions(monkeypatch, missing):
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=71))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 72 + device)
+    assert B._stream_handle(None) == 72
+    monkeypatch.delattr(torch._C, missing)
+    assert B._stream_handle(None) == 71
+
+
 def test_library_exports_every_declared_symbol():
     lib = B.load()
     names = declared_functions()
