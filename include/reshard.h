@@ -114,10 +114,10 @@ typedef struct {
                                LDS is reserved in two halves); 0 = default, chosen per kernel
                                from its fan-out (32 waves per CU when the plan reads and
                                writes at most 144 MiB, direct chunks to one receiver 120
-                               and to more than 8 64 MiB, unaligned row gathers 256 MiB, to
+                               and to more than 8 96 MiB, unaligned row gathers 256 MiB, to
                                more than 8 receivers 96, and slots with one sender per row
                                192 at fan-out 5 and 6, 40 above, of parts of the sender's
-                               rows 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and
+                               rows, 1 KiB and wider, 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and
                                above; else direct chunks: 16 at fan-out <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
                                least 8, except unaligned row gathers with one sender per row,
                                which take 32, 16 and 8 waves at fan-out 1, 2 and above, and
@@ -319,8 +319,8 @@ int64_t reshard_plan_unaligned_gather_chunks(const reshard_plan_t *plan);
 
 /* Of reshard_plan_unaligned_gather_chunks, the number that move 16-byte
  * units of each segment with unaligned loads and stores (one receiver,
- * segments under 2 KiB on average, or two receivers of rows of 128 bytes to
- * 1 KiB from one sender; a kernel of their own), or -1 for a NULL plan. */
+ * segments under 2 KiB on average, or two receivers of rows of 64 bytes to
+ * 1, 2 or 2.5 KiB from one sender; a kernel of their own), or -1 for a NULL plan. */
 int64_t reshard_plan_unit_gather_chunks(const reshard_plan_t *plan);
 
 /* Number of workgroup chunks that transpose tiles through LDS (tasks whose

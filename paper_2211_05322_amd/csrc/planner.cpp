@@ -1035,8 +1035,9 @@ void halve_gather_tail(std::vector<Desc> &g, size_t k) {
 #define RS_UNIT_MAX_SEG 2048  // the unit gather takes mean segment widths below this (bytes)
 #endif
 // ... and, to two receivers, rows of one sender from kUnitRow2Least bytes up
-// to below kUnitRow2 (see lower_gather_unaligned)
-constexpr int64_t kUnitRow2Least = 128, kUnitRow2 = 1024;
+// to below a width that depends on how they lie (see lower_gather_unaligned)
+constexpr int64_t kUnitRow2Least = 64, kUnitRow2Parts = 2560, kUnitRow2Small = 2048, kUnitRow2 = 1024;
+constexpr int64_t kUnitSmall = int64_t(32) << 20;  // bytes read
 
 // Unaligned row gather of one group (see desc.h): segments of any widths
 // tiling the destination row (one segment per row too, when its rows are in
@@ -1196,18 +1197,24 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
     // destination slots: 8 % faster with 770-byte segments at fan-out 1, 18 %
     // with 4-byte segments among them; slower with rows of 6 KiB and more
     // from one sender.  Two receivers gain too where a row has one sender and
-    // is short, cold buffers, rows in runs / source rows whole (uint8, 60 MB,
-    // slots -> units): 180 bytes 31.2 -> 27.0 / 16.6 -> 14.5 us, 300 bytes
-    // 29.8 -> 26.0 / 16.7 -> 14.3, 777 bytes 28.5 -> 28.1 / 16.4 -> 15.3;
-    // [64,1025,1001] in 250-byte rows 46.5 -> 44.0, but 34.1 -> 37.3 with its
-    // buffers in the last-level cache.  Longer rows lose (600 MB: 1500 bytes
-    // 112.5 -> 117.3, 5001 bytes 106.7 -> 113.2), and so do shorter ones, whose
-    // rows fill their last unit badly, which the table pays for too (1-byte
-    // rows 165 -> 444, 8 58.3 -> 138.8, 15 60.4 -> 200, 17 58.8 -> 62.9, 63
-    // 58.9 -> 59.5, 130 59.0 -> 56.8).  With 32 senders per row two receivers
+    // is short, cold buffers, parts of a sender's rows / whole rows (uint8, 60
+    // MB, slots -> units): 100 bytes 28.0 -> 28.1 / 16.8 -> 14.9 us, 180 bytes
+    // 31.2 -> 27.0 / 16.6 -> 14.5, 300 bytes 29.8 -> 26.0 / 16.7 -> 14.3, 1500
+    // bytes 27.6 -> 26.7 / 16.1 -> 14.4; [64,1025,1001] in 250-byte rows 46.5
+    // -> 44.0, but 34.1 -> 37.3 with its buffers in the last-level cache; 3 to
+    // 26 MB in 100-byte rows 0.84 to 0.9 of the time.  Longer rows gain little
+    // or lose, whole rows of large tensors first (200 MB, 1500 bytes 86.0 ->
+    // 81.9 / 37.3 -> 38.6, 3001 bytes 82.7 -> 82.4 / 36.9 -> 40.0; 600 MB, 1500
+    // bytes 247 -> 245 / 112.5 -> 117.3), and shorter ones lose, whose rows
+    // fill their last unit badly, which the table pays for too (parts of 1
+    // byte 165 -> 444, 8 58.3 -> 138.8, 15 60.4 -> 200, 17 58.8 -> 62.9, 63 58.9
+    // -> 59.5; whole rows of 17 26.3 -> 38.2, 33 26.2 -> 32.4, 70 26.1 -> 26.7;
+    // 20 to 50 bytes in parts are level).  With 32 senders per row two receivers
     // lose (228 -> 249), as do 4 receivers and more.
     bool unit = nfan <= int64_t(RS_UNIT_MAX_FAN) && row_bytes < int64_t(RS_UNIT_MAX_SEG) * int64_t(ns);
-    const bool unit2 = nfan == 2 && ns == 1 && row_bytes >= kUnitRow2Least && row_bytes < kUnitRow2;
+    const bool parts = ns == 1 && !lv.empty() && lv[0].ss[0] != row_bytes;
+    const int64_t least_slots = parts ? kUnitRow2Parts : p.bytes_read <= kUnitSmall ? kUnitRow2Small : kUnitRow2;
+    const bool unit2 = nfan == 2 && ns == 1 && row_bytes >= kUnitRow2Least && row_bytes < least_slots;
     unit = unit || (unit2 && !p.shortest_table);
     uint32_t upr = 0;  // units per row
     bool unit_short = false;
@@ -1298,7 +1305,7 @@ bool lower_gather_unaligned(Plan &p, const std::vector<size_t> &group, int64_t c
         p.gather_u_fanout = std::max(p.gather_u_fanout, nfan);
         p.gather_u_segs = std::max(p.gather_u_segs, int64_t(ns));
         p.gather_u_short = p.gather_u_short || (d.ds[0] & kUShortSegs) != 0;
-        p.gather_u_parts = p.gather_u_parts || (ns == 1 && !lv.empty() && lv[0].ss[0] != row_bytes);
+        p.gather_u_parts = p.gather_u_parts || (parts && row_bytes >= 1024);
     }
     return true;
 }

@@ -97,7 +97,7 @@ struct Plan {
     int64_t gather_fanout = 0; // largest receiver count among row-gather chunks
     int64_t gather_u_fanout = 0; // ... among unaligned row-gather chunks
     int64_t gather_u_segs = 0;   // most segments per row among unaligned row-gather groups
-    bool gather_u_parts = false; // some one-sender slot group reads parts of its sender's rows
+    bool gather_u_parts = false; // some one-sender slot group reads parts, 1 KiB and more, of its sender's rows
     uint64_t gather_u_bytes = 0; // destination bytes of the slot chunks, and their nominal
     uint64_t gather_u_room = 0;  //     capacity (chunks x chunk size): how full they are
     bool gather_u_short = false; // some slot group has segments under 16 bytes
@@ -124,12 +124,14 @@ inline size_t table_bytes(const Plan &p) {
 
 // Bytes read and written up to which a reshard runs with 32 waves per CU
 // instead of its kernel's cap (why: launch).  Direct chunks, by receivers:
-// to 16 cold buffers 50 MB 1.04 times as fast, 90 MB 0.97, 130 MB 0.95.
+// to 16 cold buffers 50 MB 1.04 times as fast, 90 MB 0.97, 130 MB 0.95, to 32
+// 82 MB 1.09.
 inline int64_t cached_direct_limit(int64_t fanout) {
-    return int64_t(fanout == 1 ? 120 : fanout > 8 ? 64 : 144) << 20;
+    return int64_t(fanout == 1 ? 120 : fanout > 8 ? 96 : 144) << 20;
 }
-// Slots, by receivers, senders per row, and whether a sender's rows follow one
-// another.  Rows from one sender fill the cap's fewer waves well, and the more
+// Slots, by receivers, senders per row, and whether rows are parts, 1 KiB and
+// more wide, of a sender's (shorter ones gain longer: bf16 [48,501,886] to 4,
+// 213 MB, 1.18).  Rows from one sender fill the cap's fewer waves well, and the more
 // receivers, the sooner they lose with 32 waves, parts of wider rows first
 // (times as fast, buffers cold / warm): to 2, parts 200 MB 1.02 / 0.98, 230 MB
 // 0.97 / 0.95, whole rows 1.0; to 3, 262 MB 1.2 to 1.4 / 1.05 to 1.2; to 4,

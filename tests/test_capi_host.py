@@ -570,18 +570,28 @@ def test_short_segments_take_units_at_fanout_one(case):
     assert (B.reshard_plan_unit_gather_chunks(p) > 0) == (fanout == 1), fanout
 
 
-# one sender per row to two receivers: the unit gather takes rows from 128
-# bytes to below 1 KiB; (case, units)
+# one sender per row to two receivers: the unit gather takes rows from 64
+# bytes up to below 2 KiB (small tensors), 2.5 KiB for parts of wider rows; (case, units)
 UNIT_PAIR_CASES = [
     (((4, 70, 30), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), False),    # 15-byte rows
     (((4, 70, 34), "uint8", (2,), "S^0RR", (2, 2), "RRS^0"), False),    # 17-byte rows
-    (((6, 90, 508), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), False),   # 127-byte rows in runs
-    (((6, 90, 516), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), True),    # 129-byte rows in runs
+    (((6, 90, 252), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), False),   # 63-byte rows in runs
+    (((6, 90, 260), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), True),    # 65-byte rows in runs
     (((6, 33, 1001), "uint8", (2,), "RS^0R", (4, 2), "RRS^0"), True),   # 251/250-byte rows in runs
-    (((3, 5, 1022), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), True),   # 1022-byte rows
-    (((3, 5, 1026), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # 1026-byte rows
+    (((3, 5, 2558), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), True),   # parts of 2558 bytes
+    (((3, 5, 2562), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # parts of 2562 bytes
+    (((5, 7, 1023), "float16", (3,), "S^0RR", (2, 2), "S^0RR"), True),   # whole rows of 2046 bytes
+    (((5, 7, 1025), "float16", (3,), "S^0RR", (2, 2), "S^0RR"), False),  # whole rows of 2050 bytes
     (((3, 5, 8190), "float16", (3,), "S^0RR", (2, 2), "RRS^0"), False),  # 8190-byte rows
 ]
+
+
+def test_units_to_two_receivers_of_large_tensors():
+    # whole rows, more than 32 MiB read: below 1 KiB only
+    for w, units in ((1023, True), (1025, False)):
+        p = plan_of((61, 1001, w), "uint8", (3,), "S^0RR", (2, 2), "S^0RR")
+        assert B.reshard_plan_stats(p)["bytes_read"] > 32 << 20
+        assert (B.reshard_plan_unit_gather_chunks(p) > 0) == units
 
 
 @pytest.mark.parametrize("chunk", [0, 256])
@@ -599,15 +609,15 @@ def test_waves_of_cached_reshards_as_the_header_says():
 
     def mib(senders, parts, *fanouts):
         return [lib.test_cached_limit(f, senders, parts) >> 20 for f in fanouts]
-    assert mib(0, 0, 1, 2, 8, 9, 32) == [120, 144, 144, 64, 64]
+    assert mib(0, 0, 1, 2, 8, 9, 32) == [120, 144, 144, 96, 96]
     assert mib(2, 0, 1, 2, 8, 9, 32) == mib(2, 1, 1, 2, 8, 9, 32) == [256, 256, 256, 96, 96]
     assert mib(1, 0, 1, 2, 4, 5, 6, 7, 32) == [256, 256, 256, 192, 192, 40, 40]
     assert mib(1, 1, 1, 2, 3, 4, 5, 6, 32) == [200, 200, 256, 160, 160, 40, 40]
     text = " ".join(open(HEADER).read().split())
-    for words in ("at most 144 MiB, direct chunks to one receiver 120 and to more than 8 64 MiB",
+    for words in ("at most 144 MiB, direct chunks to one receiver 120 and to more than 8 96 MiB",
                   "unaligned row gathers 256 MiB, to more than 8 receivers 96",
                   "slots with one sender per row 192 at fan-out 5 and 6, 40 above",
-                  "of parts of the sender's rows 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and above"):
+                  "of parts of the sender's rows, 1 KiB and wider, 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and above"):
         assert words in text
     with host_only.using(lib):
         for case, parts in ((((9, 160, 1233), "bfloat16", (4,), "S^0RR", (4, 2), "S^1RR"), False),
