@@ -764,10 +764,12 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
     // receivers: 122 us non-temporal, 143 plain; 1056-byte halves, not whole
     // groups: 204 and 159).  Where columns follow one another in the buffer,
     // a tile's bytes are one run, with two parts in all: not counted from
-    // 2 KiB on (fp16 [12,48,11008] to 4 receivers, 96-byte columns: 11.2 us
-    // non-temporal, 13.3 plain).  One kernel takes the plan's tiles one way
+    // 2 KiB on, up to 256-byte columns (fp16 [12,48,11008] to 4 receivers,
+    // 96-byte columns: 11.2 us non-temporal, 13.3 plain; int64 [14,39,2462] to
+    // 8, 312-byte columns, cold / warm buffers 24.6 / 23.5 non-temporal, 23.5 /
+    // 17.0 plain).  One kernel takes the plan's tiles one way
     // (see lower_once).
-    const bool dense = tr == tp.nb && tp.ds_a == tp.nb * es && ta * tp.nb * es >= 2048;
+    const bool dense = tr == tp.nb && tp.ds_a == colb && ta * colb >= 2048 && colb <= 256;
     p.n_tiles += tiles;
     if (!dense && (tp.dst_off % kTilePart || tp.ds_a % kTilePart || o1.ds % kTilePart || o2.ds % kTilePart ||
                    tr * es % kTilePart))

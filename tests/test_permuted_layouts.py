@@ -204,6 +204,17 @@ def test_transpose_stores_by_the_share_of_parts(es, n, off, plain):
         del p
 
 
+# columns that follow one another in the buffer, off 64 bytes: their tiles are
+# one run each, non-temporal up to 256 bytes a column
+@pytest.mark.parametrize("es,nb,na,plain", [(2, 48, 400, False), (8, 32, 300, False), (8, 33, 300, True), (8, 39, 300, True),
+                                            (2, 61, 400, False), (2, 129, 300, True)])
+def test_transpose_stores_of_dense_columns(es, nb, na, plain):
+    with host_only.using(host_only.plain()) as lib:
+        p = host_perm_case((3, nb, na), _TILE_DT[es], (1,), "RRR", None, (2,), "RRR", (0, 2, 1))
+        assert bool(lib.test_transpose_plain(p.handle)) == plain
+        del p
+
+
 def test_permuted_outer_dims_need_no_transpose():
     # same innermost dimension on both sides, outer dimensions swapped: the
     # direct path with per-side strides, no tile transposes
