@@ -34,7 +34,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, 8 TB/s
 METRIC = "effective resharding GB/s (read+write) and % of MI355X HBM peak, 1 GPU"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_counters.json")
 SETUP_BLOCK = 128  # workgroup size of the setup and check launches (never the timed plan's default)
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2211_05322_amd", "csrc", f) for f in ("execute.hip", "desc.h", "planner.cpp")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2211_05322_amd", "csrc", f) for f in ("execute.hip", "desc.h", "planner.cpp", "planner.hpp")]
 
 
 def kernel_hash():

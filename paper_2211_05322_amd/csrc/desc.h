@@ -197,11 +197,11 @@ constexpr TileAt tile_offsets(const Desc &d, uint32_t t, uint32_t es) {
 }
 
 // LDS image of a tile, already transposed: tile column a (16 / es rows of the
-// tile make one 16-byte slot of it) at a * tile_col_bytes, its slot j at slot
-// j ^ tile_swizzle(a): the load phase writes dwords of 16 / es neighbouring
-// columns (and 8 neighbouring vectors) at once, which the exchange spreads
-// over the banks.  Columns are counted in whole
-// vectors of rows.
+// tile make one 16-byte slot of it) at a * 16 * tile_slots_padded(slots), its
+// slot j at slot j ^ tile_swizzle(a): the load phase writes dwords of 16 / es
+// neighbouring columns (and 8 neighbouring vectors) at once, which the
+// exchange spreads over the banks.  Columns are counted in whole vectors of
+// rows.
 constexpr uint32_t tile_slots_padded(uint32_t slots) {
     return slots > 4u ? (slots + 7u) & ~7u : slots > 2u ? 4u : slots;
 }

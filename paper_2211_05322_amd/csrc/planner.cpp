@@ -818,6 +818,9 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
         out.push_back(d);
         t0 = t1;
     }
+    // (the kernel itself moves vectors at any byte address; callers were told
+    // 16 bytes where a side's strides are aligned, and the choice of tiles and
+    // of their stores counts on buffers that start so)
     p.align = std::max<int64_t>(p.align, (ald || ast) ? 16 : es);
     p.transpose_lds = std::max(p.transpose_lds, uint32_t(std::min({per, tiles, once})) * each);
 }

@@ -96,7 +96,7 @@ def test_host_transpose_tiles(dt, shape):
 
 def test_host_transpose_unaligned_rows():
     # fp16 rows of 37 elements (74 bytes): no tile row starts on a 16-byte
-    # boundary, so elements move one by one on that side
+    # boundary, and its vectors are loaded or stored where they lie
     for shape, dp in (((37, 90), (1, 0)), ((90, 37), (1, 0)), ((3, 37, 41), (2, 1, 0))):
         p = host_perm_case(shape, "float16", (1,), "R" * len(shape), None, (2,), "S^0" + "R" * (len(shape) - 1),
                            dp)
@@ -153,9 +153,10 @@ def test_transpose_table_follows_the_chunk_size():
     assert B.reshard_plan_transpose_chunks(p) == 1 << 18
 
 
-# [batch, seq, head, dim] to [batch, head, seq, dim] and back, in blocks: the
-# last block of a head short or whole, blocks wider than the rows left, rows
-# a multiple of 4 KiB apart (the receiver sets take turns) and not, one batch
+# [batch, seq, head, dim] to [batch, head, seq, dim] and back: short and whole
+# last blocks, rows that fit one block (plain order, all of the way back), rows
+# a multiple of 4 KiB apart and not, one batch.  Which layouts are taken in
+# blocks and in turns: test_block_order.py
 HEADS = [((2, 80, 32, 64), "float16", (2,), (2, 2)), ((2, 64, 32, 64), "float16", (2,), (1, 4)),
          ((3, 70, 10, 40), "float16", (2,), (2, 2)), ((1, 300, 7, 16), "float32", (1,), (1, 2)),
          ((2, 33, 16, 64), "float16", (1,), (3, 2)), ((2, 130, 8, 128), "uint8", (2,), (1, 4))]
