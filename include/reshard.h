@@ -116,7 +116,7 @@ typedef struct {
                                writes at most 144 MiB, direct chunks to one receiver 120
                                and to more than 8 96 MiB, unaligned row gathers 256 MiB, to
                                more than 8 receivers 96, and slots with one sender per row
-                               192 at fan-out 5 and 6, 40 above, of parts of the sender's
+                               192 at fan-out 5 and 6, 40 at 7 and 8, of parts of the sender's
                                rows, 1 KiB and wider, 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and
                                above; else direct chunks: 16 at fan-out <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
                                least 8, except unaligned row gathers with one sender per row,

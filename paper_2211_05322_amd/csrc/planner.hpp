@@ -139,12 +139,13 @@ inline int64_t cached_direct_limit(int64_t fanout) {
 // 1.14 / 0.92 to 1.12; to 5, whole rows 200 MB 1.11 / 1.06, 230 MB 0.93 / 0.92;
 // to 6, whole rows 180 MB 0.94 and 1.19 / 0.93 and 1.17, 262 MB 0.92, parts
 // 25 MB 1.06, 90 MB 1.05 / 0.88; to 7, 90 MB 0.93; to 8, 40 MB 1.05, 70 MB 0.92
-// to 0.95, 262 MB 0.83 to 0.89.  From several senders: to 4 and 8, 1.02 to
+// to 0.95, 262 MB 0.83 to 0.89; to 16, 110 MB 1.01, 130 MB 0.95, to 32, 82 MB
+// 1.09.  From several senders: to 4 and 8, 1.02 to
 // 1.1 up to 262 MB (bf16 [10,2157,626] to 4, 135 MB, 42.9 -> 27.0 us; 215 ->
 // 247 at 1.1 GB); to 16, 90 MB 1.02 / 0.99, 130 MB 0.96.
 inline int64_t cached_slots_limit(int64_t fanout, int64_t senders, bool parts) {
     int64_t mib = 256;
-    if (senders > 1) mib = fanout > 8 ? 96 : 256;
+    if (senders > 1 || (fanout > 8 && !parts)) mib = fanout > 8 ? 96 : 256;
     else if (parts) mib = fanout <= 2 ? 200 : fanout == 3 ? 256 : fanout <= 5 ? 160 : 40;
     else if (fanout > 4) mib = fanout <= 6 ? 192 : 40;
     return mib << 20;

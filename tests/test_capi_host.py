@@ -611,12 +611,12 @@ def test_waves_of_cached_reshards_as_the_header_says():
         return [lib.test_cached_limit(f, senders, parts) >> 20 for f in fanouts]
     assert mib(0, 0, 1, 2, 8, 9, 32) == [120, 144, 144, 96, 96]
     assert mib(2, 0, 1, 2, 8, 9, 32) == mib(2, 1, 1, 2, 8, 9, 32) == [256, 256, 256, 96, 96]
-    assert mib(1, 0, 1, 2, 4, 5, 6, 7, 32) == [256, 256, 256, 192, 192, 40, 40]
+    assert mib(1, 0, 1, 2, 4, 5, 6, 7, 8, 9, 32) == [256, 256, 256, 192, 192, 40, 40, 96, 96]
     assert mib(1, 1, 1, 2, 3, 4, 5, 6, 32) == [200, 200, 256, 160, 160, 40, 40]
     text = " ".join(open(HEADER).read().split())
     for words in ("at most 144 MiB, direct chunks to one receiver 120 and to more than 8 96 MiB",
                   "unaligned row gathers 256 MiB, to more than 8 receivers 96",
-                  "slots with one sender per row 192 at fan-out 5 and 6, 40 above",
+                  "slots with one sender per row 192 at fan-out 5 and 6, 40 at 7 and 8",
                   "of parts of the sender's rows, 1 KiB and wider, 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and above"):
         assert words in text
     with host_only.using(lib):
