@@ -112,22 +112,21 @@ typedef struct {
     int32_t max_wgs_per_cu; /* cap on resident workgroups per CU, 2..32, enforced by reserving
                                LDS per workgroup and rounded down to an even count (a CU's
                                LDS is reserved in two halves); 0 = default, chosen per kernel
-                               from its fan-out (32 waves per CU when the plan reads and
-                               writes at most 144 MiB, direct chunks to one receiver 120
-                               and to more than 8 96 MiB, unaligned row gathers 256 MiB, to
-                               more than 8 receivers 96, and slots with one sender per row
-                               192 at fan-out 5 and 6, 40 at 7 and 8, of parts of the sender's
-                               rows, 1 KiB and wider, 200, 256, 160 and 40 MiB at fan-out up to 2, 3, 5 and
-                               above; else direct chunks: 16 at fan-out <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
-                               least 8, except unaligned row gathers with one sender per row,
-                               which take 32, 16 and 8 waves at fan-out 1, 2 and above, and
-                               32 at any fan-out when their chunks are under 3/4 full on
-                               average (rows in short runs); 32 for unaligned row gathers
-                               with segments under 16 bytes at fan-out up to 4; tile
-                               transposes of 4096 chunks and more: 6 workgroups, no cap for
-                               4- and 8-byte elements to one or two receivers; never below
-                               2 workgroups); -1 = no cap.  Realignment chunks never have
-                               one. */
+                               from its fan-out (32 waves per CU when the plan reads and writes at
+                               most 144 MiB, direct chunks to one receiver 120 and to more than 8 96
+                               MiB, unaligned row gathers 256 MiB, to more than 8 receivers 96, and
+                               slots with one sender per row 192 at fan-out 5 and 6, 40 at 7 and 8,
+                               of parts of the sender's rows, 1 KiB and wider, 200, 256, 160 and 40
+                               MiB at fan-out up to 2, 3, 5 and above; else direct chunks: 16 at
+                               fan-out <= 2, 8 above; both row-gather kinds: 64 / fan-out waves, at
+                               least 8, except unaligned row gathers with one sender per row, which
+                               take 32, 16 and 8 waves at fan-out 1, 2 and above, and 32 at any fan-out
+                               when their chunks are under 3/4 full on average (rows in short
+                               runs); 32 for unaligned row gathers with segments under 16 bytes at
+                               fan-out up to 4; tile transposes of 4096 chunks and more: 6
+                               workgroups, no cap for 4- and 8-byte elements to one or two
+                               receivers; never below 2 workgroups); -1 = no cap. Realignment chunks
+                               never have one. */
     int32_t gather_band;    /* row-gather chunks: column segments per band (>= 0); the chunks
                                of a row group cover one band of the destination rows after
                                another; 0 = whole rows (default) */
