@@ -1030,9 +1030,14 @@ __device__ __forceinline__ void store_low(RS_GLOBAL unsigned char *q, u32x4 y, u
 // S^{01}, cold buffers, non-temporal / plain stores: chunks in turn 280 / 257
 // us, runs of 8 214 / 199, runs of 16 213 / 194; the kernel before 516).
 // Other plans keep non-temporal stores, which beat plain ones there (int64
-// 650 x 4480 transposed to 8 receivers 35 against 42 us).  Runs of 32 and 64
-// were level with 16 on large plans; with few chunks they leave XCDs idle.
-constexpr uint32_t kTGroup = 16;
+// 650 x 4480 transposed to 8 receivers 35 against 42 us).  Runs of 16, 32, 64
+// and 128: that tensor 195, 193, 193, 194 us; bf16 [8,2047,4098], whose chunks
+// also share source lines, cold / warm buffers 56.3 / 47.7, 53.6 / 45.0, 54.5 /
+// 44.3, 56.7 / 44.7; [24,240,8128] from [batch, hidden, seq] 44.1 / 40.7, 42.1 /
+// 33.7, 39.9 / 28.8, 39.9 / 28.9.  With few chunks long runs leave XCDs idle
+// (fp16, 90 MB to 4 receivers, 1152 chunks 20.7, 21.7, 25.4, 27.9; runs of 18
+// 23.4): at least 8 runs per XCD, of half the length under 2048 chunks.
+constexpr uint32_t kTGroup = 32;
 
 // tile_put: the vectors x of rows b .. b + R - 1 (b a multiple of R), tile
 // columns a0 .. a0 + 16 / ES - 1, to the LDS image.
@@ -1532,7 +1537,9 @@ reshard_status_t launch(const Plan &p, const Desc *descs, const int32_t *fan, co
         a.descs = descs + n_direct + n_gather + n_gather_u;
         const uint32_t tblock = block < 256u ? block : 256u;
         const uint32_t lds = transpose_launch_lds(p, user_lds);
-        a.group = p.transpose_plain ? std::max(1u, std::min<uint32_t>(kTGroup, n_transpose / 64u)) : 1u;
+        a.group = !p.transpose_plain      ? 1u
+                  : n_transpose >= 2048u ? kTGroup
+                                         : std::max(1u, std::min(kTGroup / 2u, n_transpose / 64u));
         const auto go = [&](auto es, auto fan, auto plain) {
             return launch_one(reshard_transpose_kernel<NPTR, decltype(es)::value, decltype(fan)::value, decltype(plain)::value>,
                               a, n_transpose, remap, tblock, lds, stream, 8u * a.group);
