@@ -617,6 +617,8 @@ void block_emit(Plan &p, const Piece &pc, int32_t src_buf, int64_t fan_off, int6
 #define RS_TMAXW_LOG2 2u  // widest tile along B: 4 x 128 bytes
 #endif
 constexpr int64_t kTilePart = 64;         // bytes memory writes as one (see emit_transpose)
+constexpr int64_t kTilePartSmall = 32;    // ... to one receiver, where the plan reads at most
+constexpr int64_t kTileSmall = int64_t(48) << 20;  // this many bytes
 constexpr int64_t kTileGrow = 16384;      // bytes of a tile that is narrow along one extent, at most
 constexpr int64_t kTileMaxSide = 1024;    // ... and its other side, at most
 
@@ -764,15 +766,19 @@ void emit_transpose(Plan &p, const TPiece &tp, int32_t src_buf, int64_t fan_off,
     // receivers: 122 us non-temporal, 143 plain; 1056-byte halves, not whole
     // groups: 204 and 159).  Where columns follow one another in the buffer,
     // a tile's bytes are one run, with two parts in all: not counted from
-    // 2 KiB on, up to 256-byte columns (fp16 [12,48,11008] to 4 receivers,
-    // 96-byte columns: 11.2 us non-temporal, 13.3 plain; int64 [14,39,2462] to
-    // 8, 312-byte columns, cold / warm buffers 24.6 / 23.5 non-temporal, 23.5 /
-    // 17.0 plain).  One kernel takes the plan's tiles one way
+    // 2 KiB on, to more than 4 receivers up to 256-byte columns (fp16
+    // [12,48,11008] to 4 receivers, 96-byte columns: 11.2 us non-temporal, 13.3
+    // plain; int64 in 312-byte columns, cold / warm buffers, [14,39,2462] to 8
+    // 24.6 / 23.5 non-temporal, 23.5 / 17.0 plain; [32,39,496] to 4 0.84 of the
+    // plain time non-temporal).  Halves of a group are cheap in small tensors to one receiver
+    // (4064-byte columns, cold / warm: bf16 [6,240,8128] 13.4 / 10.1 non-temporal
+    // in turn, 14.0 / 9.9 plain in runs; fp32, 45 MB, 12.8 / 8.7 and 14.2 / 11.6).
+    // One kernel takes the plan's tiles one way
     // (see lower_once).
-    const bool dense = tr == tp.nb && tp.ds_a == colb && ta * colb >= 2048 && colb <= 256;
+    const bool dense = tr == tp.nb && tp.ds_a == colb && ta * colb >= 2048 && (colb <= 256 || nfan <= 4);
     p.n_tiles += tiles;
-    if (!dense && (tp.dst_off % kTilePart || tp.ds_a % kTilePart || o1.ds % kTilePart || o2.ds % kTilePart ||
-                   tr * es % kTilePart))
+    const int64_t part = nfan == 1 && p.bytes_read <= kTileSmall ? kTilePartSmall : kTilePart;
+    if (!dense && (tp.dst_off % uint64_t(part) || tp.ds_a % part || o1.ds % part || o2.ds % part || tr * es % part))
         p.n_part_tiles += tiles;
     const FastDiv fsl = make_fastdiv(uint32_t((tr * es + 15) / 16));
     d.pad[0] = vl2 | (fsl.shift << 8);

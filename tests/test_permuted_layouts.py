@@ -205,13 +205,23 @@ def test_transpose_stores_by_the_share_of_parts(es, n, off, plain):
         del p
 
 
-# columns that follow one another in the buffer, off 64 bytes: their tiles are
-# one run each, non-temporal up to 256 bytes a column
-@pytest.mark.parametrize("es,nb,na,plain", [(2, 48, 400, False), (8, 32, 300, False), (8, 33, 300, True), (8, 39, 300, True),
-                                            (2, 61, 400, False), (2, 129, 300, True)])
-def test_transpose_stores_of_dense_columns(es, nb, na, plain):
+# columns of 32-byte multiples off 64: plain, but for small tensors to one receiver
+@pytest.mark.parametrize("shape,fan,plain", [((1, 2032, 80), 1, False), ((1, 2032, 80), 2, True), ((1, 2040, 80), 1, True),
+                                             ((6, 2032, 2100), 1, True)])
+def test_transpose_stores_of_half_groups(shape, fan, plain):
     with host_only.using(host_only.plain()) as lib:
-        p = host_perm_case((3, nb, na), _TILE_DT[es], (1,), "RRR", None, (2,), "RRR", (0, 2, 1))
+        p = B.reshard_plan(shape, "float16", (1,), "RRR", (fan,), "RRR", dst_perm=(0, 2, 1))
+        assert bool(lib.test_transpose_plain(p.handle)) == plain
+        del p
+
+
+# columns that follow one another in the buffer, off 64 bytes: their tiles are
+# one run each, non-temporal up to 256 bytes a column or 4 receivers
+@pytest.mark.parametrize("es,nb,na,fan,plain", [(2, 48, 400, 5, False), (8, 32, 5500, 5, False), (8, 33, 5500, 5, True),
+                                                (8, 33, 5500, 4, False), (8, 39, 300, 8, True), (2, 61, 400, 5, False)])
+def test_transpose_stores_of_dense_columns(es, nb, na, fan, plain):
+    with host_only.using(host_only.plain()) as lib:
+        p = host_perm_case((3, nb, na), _TILE_DT[es], (1,), "RRR", None, (fan,), "RRR", (0, 2, 1))
         assert bool(lib.test_transpose_plain(p.handle)) == plain
         del p
 
