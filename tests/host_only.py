@@ -34,7 +34,8 @@ def build(out, **limits):
 @functools.lru_cache(maxsize=None)
 def plain():
     """The product's host code and limits."""
-    return build(os.path.join(tempfile.mkdtemp(prefix="reshard_host_"), "host.so"))
+    with tempfile.TemporaryDirectory(prefix="reshard_host_") as d:
+        return build(os.path.join(d, "host.so"))  # stays mapped
 
 
 @contextlib.contextmanager
